@@ -814,44 +814,45 @@ extern "C" gsr_status gsr_seed_triangulate(int64_t n, int32_t n_neighbours, cons
 
 namespace {
 struct KnnLayout {
-    size_t bpart, grid, cell_count, cell_start, cell_of, rank, sorted, total;
-    size_t opart, fine_count, fine_start, fine_of, fine_rank, fine_pts, cell_pts, scan_tot, bf_list, bf_count;
-    int64_t max_cells;
-    int32_t table_bits;
+    size_t box, tree, split, total_b, bucket_leaf, row, bucket_of, super_lo, super_hi, leaf_lo, leaf_hi, groups, placed, pts, mom,
+        total;
+    int64_t max_leaves;
+    int32_t buckets, per_block;
 };
 
 KnnLayout knn_layout(int64_t n)
 {
     KnnLayout L{};
-    L.max_cells = 4 * n + 64;
+    // the sample costs (4 buckets)^2 comparisons and the bitonic sort grows
+    // with the bucket: a few hundred to 2,000 points a bucket
+    L.buckets = n <= 131072 ? 256 : (n <= (1 << 21) ? 1024 : 4096);
+    L.per_block = n <= 131072 ? 1024 : (n <= (1 << 21) ? 2048 : 8192);
+    // every bucket ends in a leaf of its own
+    L.max_leaves = (n + 63) / 64 + L.buckets;
+    const size_t blocks = (size_t)((n + L.per_block - 1) / L.per_block), nb = (size_t)L.buckets,
+                 slots = (size_t)L.max_leaves * 64;
     size_t o = 0;
     auto take = [&](size_t bytes) {
         size_t at = o;
         o = align256(o + (bytes ? bytes : 1));
         return at;
     };
-    L.bpart = take(sizeof(float) * 8 * GSR_KNN_BLOCKS);
-    L.grid = take(sizeof(KnnGrid));
-    L.cell_count = take(sizeof(uint32_t) * (size_t)(L.max_cells + 1));
-    L.cell_start = take(sizeof(uint32_t) * (size_t)(L.max_cells + 1));
-    L.cell_of = take(sizeof(uint32_t) * (size_t)n);
-    L.rank = take(sizeof(uint32_t) * (size_t)n);
-    L.sorted = take(sizeof(uint32_t) * (size_t)n);
-    // fine grid: a hash table of at least two buckets per seed
-    L.table_bits = 10;
-    while (((int64_t)1 << L.table_bits) < 2 * n) ++L.table_bits;
-    const int64_t T = (int64_t)1 << L.table_bits;
-    L.opart = take(sizeof(double) * GSR_KNN_BLOCKS);
-    L.fine_count = take(sizeof(uint32_t) * GSR_KNN_LEVELS * (size_t)(T + 1));
-    L.fine_start = take(sizeof(uint32_t) * GSR_KNN_LEVELS * (size_t)(T + 1));
-    L.fine_of = take(sizeof(uint32_t) * GSR_KNN_LEVELS * (size_t)n);
-    L.fine_rank = take(sizeof(uint32_t) * GSR_KNN_LEVELS * (size_t)n);
-    L.fine_pts = take(sizeof(float) * 4 * GSR_KNN_LEVELS * (size_t)n);
-    L.cell_pts = take(sizeof(float) * 4 * (size_t)n);
-    const int64_t scan_blocks = std::max((L.max_cells + 1 + 1023) / 1024, (T + 1 + 1023) / 1024);
-    L.scan_tot = take(sizeof(uint32_t) * (size_t)scan_blocks);
-    L.bf_list = take(sizeof(uint32_t) * (size_t)n);
-    L.bf_count = take(sizeof(uint32_t));
+    L.box = take(sizeof(float) * 8 * GSR_KNN_BLOCKS);
+    L.tree = take(sizeof(KnnTree));
+    L.split = take(sizeof(uint64_t) * nb);
+    L.total_b = take(sizeof(uint32_t) * nb);
+    L.bucket_leaf = take(sizeof(uint32_t) * (nb + 1));
+    L.row = take(sizeof(uint32_t) * nb * blocks);
+    L.bucket_of = take(sizeof(uint16_t) * (size_t)n);
+    const size_t leaves = (size_t)L.max_leaves, supers = (leaves + 63) / 64;
+    L.super_lo = take(sizeof(float4) * supers);
+    L.super_hi = take(sizeof(float4) * supers);
+    L.leaf_lo = take(sizeof(float4) * leaves);
+    L.leaf_hi = take(sizeof(float4) * leaves);
+    L.groups = take(sizeof(float) * 48 * leaves);
+    L.placed = take(sizeof(float4) * slots);
+    L.pts = take(sizeof(float4) * slots);
+    L.mom = take(sizeof(double) * 10 * slots);
     L.total = o;
     return L;
 }
@@ -872,25 +873,24 @@ static KnnArgs knn_args(int64_t n, const float* mean, const int32_t* valid, floa
     a.mean = mean;
     a.valid = valid;
     a.floor_scale = floor_scale;
-    a.max_cells = L.max_cells;
-    a.bpart = (float*)(ws + L.bpart);
-    a.grid = (KnnGrid*)(ws + L.grid);
-    a.cell_count = (uint32_t*)(ws + L.cell_count);
-    a.cell_start = (uint32_t*)(ws + L.cell_start);
-    a.cell_of = (uint32_t*)(ws + L.cell_of);
-    a.rank = (uint32_t*)(ws + L.rank);
-    a.sorted = (uint32_t*)(ws + L.sorted);
-    a.table_bits = L.table_bits;
-    a.opart = (double*)(ws + L.opart);
-    a.fine_count = (uint32_t*)(ws + L.fine_count);
-    a.fine_start = (uint32_t*)(ws + L.fine_start);
-    a.fine_of = (uint32_t*)(ws + L.fine_of);
-    a.fine_rank = (uint32_t*)(ws + L.fine_rank);
-    a.fine_pts = (float4*)(ws + L.fine_pts);
-    a.cell_pts = (float4*)(ws + L.cell_pts);
-    a.scan_tot = (uint32_t*)(ws + L.scan_tot);
-    a.bf_list = (uint32_t*)(ws + L.bf_list);
-    a.bf_count = (uint32_t*)(ws + L.bf_count);
+    a.buckets = L.buckets;
+    a.per_block = L.per_block;
+    a.max_leaves = L.max_leaves;
+    a.box = (float*)(ws + L.box);
+    a.tree = (KnnTree*)(ws + L.tree);
+    a.split = (uint64_t*)(ws + L.split);
+    a.total = (uint32_t*)(ws + L.total_b);
+    a.bucket_leaf = (uint32_t*)(ws + L.bucket_leaf);
+    a.row = (uint32_t*)(ws + L.row);
+    a.bucket_of = (uint16_t*)(ws + L.bucket_of);
+    a.super_lo = (float4*)(ws + L.super_lo);
+    a.super_hi = (float4*)(ws + L.super_hi);
+    a.leaf_lo = (float4*)(ws + L.leaf_lo);
+    a.leaf_hi = (float4*)(ws + L.leaf_hi);
+    a.groups = (float*)(ws + L.groups);
+    a.placed = (float4*)(ws + L.placed);
+    a.pts = (float4*)(ws + L.pts);
+    a.mom = (double*)(ws + L.mom);
     return a;
 }
 
@@ -926,7 +926,6 @@ extern "C" gsr_status gsr_seed_frame(int64_t n, const float* mean, const int32_t
     const KnnLayout L = knn_layout(n);
     if (workspace_bytes < L.total) return fail(GSR_EINVAL, "workspace too small");
     KnnArgs a = knn_args(n, mean, valid, floor_scale, workspace, L);
-    a.fine_levels = 1;  // only the level of cells of the radius
     FrameArgs f{};
     for (int k = 0; k < 12; ++k) f.P[k] = P_ref[k];
     for (int k = 0; k < 3; ++k) f.centre[k] = centre_ref[k];

@@ -206,8 +206,8 @@ struct CompactArgs {
 };
 
 #define GSR_SEED_MAX_NEIGHBOURS 8
-#define GSR_KNN_BLOCKS 256          // blocks of the seeds' bounding-box pass
-#define GSR_KNN_LEVELS 8            // fine hashed grid levels (cell sizes h1 * 2^l)
+#define GSR_KNN_BLOCKS 256          // blocks of the points' bounding-box pass
+#define GSR_KNN_SMALL 16384         // up to this many points are searched without a tree
 
 struct SeedView {
     double P[12];              // 3x4 projection matrix K [R | t], row-major
@@ -235,14 +235,11 @@ struct SeedArgs {
     float* kappa_bar;          // [n]
 };
 
-struct KnnGrid {
-    double origin[3];
-    double h;                  // coarse cell size
-    int32_t dims[3];           // coarse grid
-    int64_t cells;
-    int64_t count;             // valid seeds
-    double h1, inv_h1;         // fine cell size (when fine)
-    int32_t fine;
+// the points' Morton cells, and how many leaves of 64 points they make
+struct KnnTree {
+    double lo[3];              // least coordinates of the finite valid points
+    double scale;              // cells per unit length
+    int32_t leaves;
 };
 
 struct KnnArgs {
@@ -250,31 +247,27 @@ struct KnnArgs {
     const float* mean;         // [3][n]
     const int32_t* valid;      // [n]
     float floor_scale;
-    int64_t max_cells;
-    float* bpart;              // [GSR_KNN_BLOCKS][8]
-    KnnGrid* grid;
-    uint32_t* cell_count;      // [max_cells + 1]
-    uint32_t* cell_start;      // [max_cells + 1]
-    uint32_t* cell_of;         // [n]
-    uint32_t* rank;            // [n]
-    uint32_t* sorted;          // [n]
-    int32_t table_bits;        // fine grid: hash table of 2^table_bits buckets
-    double* opart;             // [GSR_KNN_BLOCKS]
-    uint32_t* fine_count;      // [GSR_KNN_LEVELS][2^table_bits + 1]
-    uint32_t* fine_start;      // [GSR_KNN_LEVELS][2^table_bits + 1]
-    uint32_t* fine_of;         // [GSR_KNN_LEVELS][n]
-    uint32_t* fine_rank;       // [GSR_KNN_LEVELS][n]
-    float4* fine_pts;          // [GSR_KNN_LEVELS][n]: (x, y, z, index bits) in fine-bucket order
-    float4* cell_pts;          // [n]: the same in coarse-cell order
-    int32_t* nn_index;         // [n] or null: each seed's nearest other seed (-1: none)
-    uint32_t* scan_tot;        // block totals of the scans
-    uint32_t* bf_list;         // [n] queries left to the exhaustive search
-    uint32_t* bf_count;        // their number
-    float* log_scale;          // [3][n]
-    int32_t fine_levels;       // fine levels built (0: all GSR_KNN_LEVELS)
+    int32_t buckets;           // buckets of the sample sort: 256, 1024 or 4096
+    int32_t per_block;         // points per block of the counting passes
+    int64_t max_leaves;
+    float* box;                // [GSR_KNN_BLOCKS][8] partial boxes
+    KnnTree* tree;
+    uint64_t* split;           // [buckets] least code of each bucket
+    uint32_t* total;           // [buckets] points
+    uint32_t* bucket_leaf;     // [buckets + 1] first leaf
+    uint32_t* row;             // [blocks][buckets] a block's offset inside each bucket
+    uint16_t* bucket_of;       // [n] (0xffff: invalid)
+    float4 *super_lo, *super_hi;    // [ceil(max_leaves / 64)] boxes of 64 consecutive leaves
+    float4 *leaf_lo, *leaf_hi;      // [max_leaves] boxes
+    float* groups;             // [max_leaves][8][6]: lo, hi of a leaf's groups of 8 points
+    float4* placed;            // [max_leaves * 64]: (x, y, z, index bits) by bucket
+    float4* pts;               // [max_leaves * 64]: the same, sorted
+    double* mom;               // [10][leaves * 64] neighbour moments
+    float* log_scale;          // [3][n] or null
+    int32_t* nn_index;         // [n] or null: each point's nearest other (-1: none)
 };
 
-// anisotropic initialisation of the seeds (after the coarse grid of KnnArgs)
+// anisotropic initialisation of the seeds
 struct FrameArgs {
     double P[12];              // reference projection, row-major 3 x 4
     double centre[3];          // reference camera centre
