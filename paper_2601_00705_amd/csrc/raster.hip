@@ -25,6 +25,18 @@
 // tile's totals to the slot's double accumulators with one atomic
 // instruction (plus one).  Per-pixel work is branch-free (selects); an entry
 // no lane of the wave needs is skipped as a whole.
+//
+// Both passes are bound by VALU issue where the tiles fill the chip (an entry
+// costs ~100 instructions of the forward's four pixels a lane, ~260 of the
+// backward's, over half of which go to the nine sums of two pixels' partials
+// and their reduction), and by one wave's serial chain where they do not.
+// Everything about an entry that the lanes share (its tile, position, slot,
+// whether it may clamp, whether a lane needs it) is therefore kept on the
+// scalar unit, and decided once per batch where it can be: with loops and
+// branches left divergent, predicates in vector registers and the clamp and
+// position tests on every entry, the backward took 2804 us on ten 1200x680
+// views of 1M Gaussians (now 2632) and 10325 us on 36 views of 3M (now 9346),
+// the forward 1310 us (now 1277).
 #include "kernels.h"
 
 namespace gsr {
@@ -32,11 +44,23 @@ namespace gsr {
 #define GSR_LOG2E 1.4426950408889634f
 #define GSR_LN2 0.69314718055994531f
 
+// A value that every lane holds alike, in a scalar register: the compiler
+// takes what a vector load returns as different between lanes, and the loops
+// and branches that depend on it as divergent (exec-mask bookkeeping and
+// register copies on every entry).
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Predicates of the lanes are kept as 64-bit masks in scalar registers and
+// used by the selects from there; as bools they go through a vector register
+// wherever two paths meet.
+__device__ __forceinline__ uint64_t lanes(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 struct __align__(16) LdsRec {
     float4 p0;  // c0, gx, gy, a2   (power2 at the tile centre and its gradient; a2 = k A)
     float4 p1;  // b2, c2, o, thr   (b2 = 2 k B, c2 = k C, thr = log2(alpha_min / o))
     float4 p2;  // r, g, b, slot bits
-    float4 p3;  // ox, oy, 1/o, -   (tile centre - projected centre)
+    float4 p3;  // ox, oy, 1/o, 2 c2   ((ox, oy) = tile centre - projected centre)
 };
 
 // Stages the record of `slot` for the tile centred at (xc, yc).  With
@@ -84,9 +108,10 @@ __device__ __forceinline__ Staged load_staged(const RasterArgs& a, uint32_t slot
     return t;
 }
 
+// Returns the entry's opacity.
 template <bool MIXED>
-__device__ __forceinline__ void stage_record(const RasterArgs& a, uint32_t slot, double xc, double yc,
-                                             LdsRec& r)
+__device__ __forceinline__ float stage_record(const RasterArgs& a, uint32_t slot, double xc, double yc,
+                                              LdsRec& r)
 {
     const Staged sr = load_staged<MIXED>(a, slot);
     const double k = -0.5 * 1.4426950408889634;
@@ -97,7 +122,8 @@ __device__ __forceinline__ void stage_record(const RasterArgs& a, uint32_t slot,
                        (float)(k * sr.A));
     r.p1 = make_float4((float)(2.0 * k * sr.B), (float)(k * sr.C), sr.o, thr);
     r.p2 = make_float4(sr.r, sr.g, sr.b, __uint_as_float(slot));
-    r.p3 = make_float4((float)ox, (float)oy, 1.0f / sr.o, 0.0f);
+    r.p3 = make_float4((float)ox, (float)oy, 1.0f / sr.o, 2.0f * r.p1.y);
+    return sr.o;
 }
 
 // writes one colour value of the image (float32, or binary16 when MIXED)
@@ -183,16 +209,24 @@ __device__ __forceinline__ TileCtx<PPT> tile_ctx_at(const RasterArgs& a, int til
 template <int PPT>
 __device__ __forceinline__ TileCtx<PPT> tile_ctx(const RasterArgs& a)
 {
-    return tile_ctx_at<PPT>(a, (int)a.order[blockIdx.x], 0);
+    return tile_ctx_at<PPT>(a, uniform((int)a.order[blockIdx.x]), 0);
+}
+
+// the tile's pairs, empty after an overflow
+__device__ __forceinline__ uint2 tile_range(const RasterArgs& a, int tile)
+{
+    const uint2 r = a.ranges[tile];
+    return make_uint2((uint32_t)uniform((int)r.x), (uint32_t)uniform((int)r.y));
 }
 
 // Whether an entry of opacity o can have a clamped alpha anywhere (alpha =
-// o G with G <= 1): o >= alpha_max.  Both are positive floats, whose order is
-// their bit patterns' order, so the test runs on the scalar unit with the
-// first lane's o (the staged record is the same for every lane).
+// o G with G <= 1): !(o < alpha_max).  Both are positive floats, whose order
+// is their bit patterns' order (a NaN of either sign is above all of them, as
+// unsigned numbers), so the test runs on the scalar unit with the first
+// lane's o (the staged record is the same for every lane).
 __device__ __forceinline__ bool may_clamp(float o, float amax)
 {
-    return __builtin_amdgcn_readfirstlane(__float_as_int(o)) >= __float_as_int(amax);
+    return (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(o)) >= __float_as_uint(amax);
 }
 
 // Walks the batch in LDS for the lane's pixels.  A pixel that has stopped
@@ -200,7 +234,8 @@ __device__ __forceinline__ bool may_clamp(float o, float amax)
 // power2 >= thr fails for it without a per-pixel flag.  Reaching T_min is
 // rare (once per pixel at most), so the common step applies every passing
 // entry and a wave-uniform branch undoes the blend of stopping pixels.
-template <int PPT, bool COUNT>
+// CLAMPS: the batch holds an entry that may clamp, so every entry is asked.
+template <int PPT, bool COUNT, bool CLAMPS>
 __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t pos0, float amax, float tmin,
                                           float dx, float (&dy)[PPT], float (&T)[PPT], float (&C0)[PPT],
                                           float (&C1)[PPT], float (&C2)[PPT], uint32_t (&last)[PPT],
@@ -216,45 +251,49 @@ __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t p
         const LdsRec r = rec[e];
         const ColTerms ct = col_terms(r, dx);
         float p2[PPT];
-        bool pass[PPT];
-        uint64_t any = 0;
+        uint64_t pass[PPT], any = 0;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             p2[k] = power2(ct, r.p1.y, dy[k]);
-            pass[k] = p2[k] >= r.p1.w;
-            any |= __builtin_amdgcn_ballot_w64(pass[k]);
+            pass[k] = lanes(p2[k] >= r.p1.w);
+            any |= pass[k];
         }
         if (any == 0) continue;
         float ab[PPT], Tn[PPT];
-        bool stop[PPT];
-        uint64_t any_stop = 0;
+        if (CLAMPS && may_clamp(r.p1.z, amax)) {
+#pragma unroll
+            for (int k = 0; k < PPT; ++k)
+                ab[k] = in(pass[k]) ? fminf(amax, r.p1.z * __builtin_amdgcn_exp2f(p2[k])) : 0.0f;
+        } else {
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) ab[k] = in(pass[k]) ? r.p1.z * __builtin_amdgcn_exp2f(p2[k]) : 0.0f;
+        }
+        uint64_t stop[PPT], any_stop = 0;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
-            const float alpha = fminf(amax, r.p1.z * __builtin_amdgcn_exp2f(p2[k]));
-            ab[k] = pass[k] ? alpha : 0.0f;
             Tn[k] = __builtin_fmaf(-T[k], ab[k], T[k]);
-            stop[k] = Tn[k] < tmin;
-            any_stop |= __builtin_amdgcn_ballot_w64(stop[k]);
+            stop[k] = lanes(Tn[k] < tmin);
+            any_stop |= stop[k];
         }
         if (any_stop != 0) {
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
-                ab[k] = stop[k] ? 0.0f : ab[k];
-                Tn[k] = stop[k] ? T[k] : Tn[k];
-                dy[k] = stop[k] ? __builtin_nanf("") : dy[k];
+                ab[k] = in(stop[k]) ? 0.0f : ab[k];
+                Tn[k] = in(stop[k]) ? T[k] : Tn[k];
+                dy[k] = in(stop[k]) ? __builtin_nanf("") : dy[k];
+                pass[k] &= ~stop[k];
             }
         }
         const uint32_t pos1 = pos0 + (uint32_t)e + 1u;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
-            const bool blend = pass[k] & !stop[k];
             const float wgt = ab[k] * T[k];
             C0[k] = __builtin_fmaf(r.p2.x, wgt, C0[k]);
             C1[k] = __builtin_fmaf(r.p2.y, wgt, C1[k]);
             C2[k] = __builtin_fmaf(r.p2.z, wgt, C2[k]);
             T[k] = Tn[k];
-            last[k] = blend ? pos1 : last[k];
-            if (COUNT) nb[k] += blend ? 1u : 0u;
+            last[k] = in(pass[k]) ? pos1 : last[k];
+            if (COUNT) nb[k] += in(pass[k]) ? 1u : 0u;
         }
     }
 }
@@ -265,8 +304,8 @@ template <int PPT, int GSR_BATCH, bool COUNT, bool MIXED>
 __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>& c, LdsRec* rec)
 {
     const int lane = threadIdx.x;
-    const bool overflow = a.counters->overflow != 0u;
-    const uint2 range = overflow ? make_uint2(0u, 0u) : a.ranges[c.tile];
+    const bool overflow = uniform((int)a.counters->overflow) != 0;
+    const uint2 range = overflow ? make_uint2(0u, 0u) : tile_range(a, c.tile);
     const float amax = a.cfg.alpha_max, tmin = a.cfg.T_min;
     float T[PPT], C0[PPT], C1[PPT], C2[PPT], dy[PPT];
     uint32_t last[PPT], nb[PPT];
@@ -282,14 +321,20 @@ __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>
 #pragma unroll
         for (int k = 0; k < PPT; ++k) live |= __builtin_amdgcn_ballot_w64(dy[k] == dy[k]);
         if (live == 0) break;
+        bool may = false;
 #pragma unroll
         for (int r = 0; r < GSR_BATCH / 64; ++r) {
             const uint32_t j = base + lane + 64 * r;
-            if (j < range.y) stage_record<MIXED>(a, a.vals[j], c.xc, c.yc, rec[lane + 64 * r]);
+            if (j < range.y)
+                may |= !(stage_record<MIXED>(a, a.vals[j], c.xc, c.yc, rec[lane + 64 * r]) < amax);
         }
+        const bool clamps = lanes(may) != 0;
         __syncthreads();
         const int cnt = (int)min((uint32_t)GSR_BATCH, range.y - base);
-        fwd_batch<PPT, COUNT>(rec, cnt, base - range.x, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+        // with 8 pixels per lane a second copy of the loop costs registers
+        // that the waves need more (96 and spills instead of 88)
+        if (PPT > 4 || clamps) fwd_batch<PPT, COUNT, true>(rec, cnt, base - range.x, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+        else fwd_batch<PPT, COUNT, false>(rec, cnt, base - range.x, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
         __syncthreads();
     }
 #pragma unroll
@@ -365,12 +410,12 @@ __device__ __forceinline__ int long_tiles(const RasterArgs& a, int total_tiles, 
 }
 
 template <int PPT, int GSR_BATCH, bool COUNT, bool MIXED>
-__global__ __launch_bounds__(64) void k_raster_fwd(RasterArgs a)
+__global__ __launch_bounds__(64, 5) void k_raster_fwd(RasterArgs a)
 {
     __shared__ LdsRec rec[GSR_BATCH];
     const TileCtx<PPT> c = tile_ctx<PPT>(a);
     if (FwdSplit<PPT>::parts > 1) {
-        const uint2 r = a.ranges[c.tile];
+        const uint2 r = tile_range(a, c.tile);
         if (r.y - r.x >= long_threshold(a)) return;  // composited in parts by k_raster_fwd_long
     }
     fwd_tile<PPT, GSR_BATCH, COUNT, MIXED>(a, c, rec);
@@ -383,7 +428,7 @@ __global__ __launch_bounds__(64) void k_raster_fwd(RasterArgs a)
 // priority: each carries a whole list and ends the forward, while the short
 // tiles' waves beside them on the same SIMDs can wait a little.
 template <int PPT, int GSR_BATCH, bool COUNT, bool MIXED>
-__global__ __launch_bounds__(64) void k_raster_fwd_long(RasterArgs a, int total_tiles)
+__global__ __launch_bounds__(64, 5) void k_raster_fwd_long(RasterArgs a, int total_tiles)
 {
     using F = FwdSplit<PPT>;
     constexpr int S = F::parts, Q = F::ppt, S2 = F::parts2, Q2 = F::ppt2;
@@ -511,15 +556,15 @@ template <bool DET>
 __device__ __forceinline__ void add_field(const RasterArgs& a, uint32_t slot, int f, float value)
 {
     if (DET) fixed_add(a.acc + GSR_G2 * GSR_FIX_LIMBS * (int64_t)slot + f, GSR_G2, value);
-    else atomic_add_f64(&a.grad2d[GSR_G2 * (int64_t)slot + f], (double)value);
+    else atomic_add_f64(a.grad2d + GSR_G2 * (uint64_t)slot + (uint32_t)f, (double)value);
 }
 
 // The ninth field (the blue colour partial) of a reduced entry waits for the
 // next reduced entry's, and the two are summed over the wave in one chain
 // (wave_sum_pair); slot is wave-uniform.
 struct PendingField {
-    bool have;
-    uint32_t slot;
+    int have;
+    int slot;
     float w;
 };
 
@@ -537,7 +582,7 @@ struct PendingField {
 // no gradient (dd = 0) but still attenuates.
 template <int PPT, bool CLAMP, bool DET>
 __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, const ColTerms& ct,
-                                          const float (&p2)[PPT], const bool (&on)[PPT], float amax,
+                                          const float (&p2)[PPT], const uint64_t (&on)[PPT], float amax,
                                           const TileCtx<PPT>& c, const float (&g0)[PPT], const float (&g1)[PPT],
                                           const float (&g2)[PPT], const float (&dy2)[PPT], float (&T)[PPT],
                                           float (&gsk)[PPT], int lane, PendingField& pend)
@@ -546,7 +591,7 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         const float a_raw = r.p1.z * __builtin_amdgcn_exp2f(p2[k]);
-        const float alpha = on[k] ? (CLAMP ? fminf(a_raw, amax) : a_raw) : 0.0f;
+        const float alpha = in(on[k]) ? (CLAMP ? fminf(a_raw, amax) : a_raw) : 0.0f;
         const float rcp = __builtin_amdgcn_rcpf(1.0f - alpha);
         const float Tb = T[k] * rcp;
         const float gcol = __builtin_fmaf(g0[k], r.p2.x, __builtin_fmaf(g1[k], r.p2.y, g2[k] * r.p2.z));
@@ -559,7 +604,7 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
         if (CLAMP) dd = a_raw < amax ? dd : 0.0f;
         gsk[k] = gsk_new;
         T[k] = Tb;
-        D += dd;
+        D = k == 0 ? dd : D + dd;
         Dy = __builtin_fmaf(dd, c.dy[k], Dy);
         Dyy = __builtin_fmaf(dd, dy2[k], Dyy);
     }
@@ -570,8 +615,9 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
     const float fx = c.dx + r.p3.x;
     const float Fy = __builtin_fmaf(r.p3.y, D, Dy);  // sum dd fy
     float v[9];
-    v[0] = __builtin_fmaf(__builtin_fmaf(2.0f * r.p0.w, c.dx, r.p0.y), D, r.p1.x * Dy);
-    v[1] = __builtin_fmaf(ct.s1, D, 2.0f * r.p1.y * Dy);
+    // (2 a2 dx as a2 (2 dx): the same product, with 2 dx a constant of the lane)
+    v[0] = __builtin_fmaf(__builtin_fmaf(r.p0.w, 2.0f * c.dx, r.p0.y), D, r.p1.x * Dy);
+    v[1] = __builtin_fmaf(ct.s1, D, r.p3.w * Dy);
     v[2] = fx * (fx * D);
     v[3] = fx * Fy;
     v[4] = __builtin_fmaf(r.p3.y, Fy + Dy, Dyy);
@@ -580,25 +626,66 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
     v[7] = c1s;
     v[8] = c2s;
     const float s = wave_sum8_transposed(v, lane);
-    const uint32_t slot = __builtin_amdgcn_readfirstlane(__float_as_uint(r.p2.w));
+    const uint32_t slot = (uint32_t)uniform(__float_as_int(r.p2.w));
     if ((lane & 7) == 0) {
         const int f = lane >> 3;
-        add_field<DET>(a, slot, f, s * (f == 5 ? r.p3.z : field_scale(f)));
+        const float value = s * (f == 5 ? r.p3.z : field_scale(f));
+        if (DET) {
+            add_field<DET>(a, slot, f, value);
+        } else {
+            // the slot's address stays scalar (left to itself the compiler
+            // folds it into a 64-bit multiply-add per lane)
+            uint64_t base = (uint64_t)a.grad2d + sizeof(double) * GSR_G2 * (uint64_t)slot;
+            asm("" : "+s"(base));
+            typedef __attribute__((address_space(1))) double global_double;
+            __builtin_amdgcn_global_atomic_fadd_f64(reinterpret_cast<global_double*>(base) + (uint32_t)f, (double)value);
+        }
     }
-    if (pend.have) {
+    if (uniform(pend.have)) {
+        // lane 1 holds the waiting entry's total, lane 33 this one's
         const float w = wave_sum_pair(pend.w, v[8]);
-        if (lane == 1) add_field<DET>(a, pend.slot, 8, w);
-        if (lane == 33) add_field<DET>(a, slot, 8, w);
-        pend.have = false;
+        if ((lane & 31) == 1) add_field<DET>(a, lane < 32 ? (uint32_t)pend.slot : slot, 8, w);
+        pend.have = 0;
     } else {
         pend.w = v[8];
-        pend.slot = slot;
-        pend.have = true;
+        pend.slot = (int)slot;
+        pend.have = 1;
+    }
+}
+
+// The staged entries rec[0, cnt), from the list's position top down.
+// CLAMPS: the batch holds an entry that may clamp, so every entry is asked
+// (alpha = o G <= o: a test uniform over the wave); FULL: every pixel of the
+// tile blended an entry at top or behind it, so no position is tested.
+template <int PPT, bool CLAMPS, bool FULL, bool DET>
+__device__ __forceinline__ void bwd_batch(const RasterArgs& a, const LdsRec* rec, int cnt, uint32_t top, float amax,
+                                          const TileCtx<PPT>& c, const uint32_t (&my_n)[PPT], const float (&g0)[PPT],
+                                          const float (&g1)[PPT], const float (&g2)[PPT], const float (&dy2)[PPT],
+                                          float (&T)[PPT], float (&gsk)[PPT], int lane, PendingField& pend)
+{
+    for (int e = 0; e < cnt; ++e) {
+        const uint32_t pos = top - (uint32_t)e;
+        const LdsRec r = rec[e];
+        const ColTerms ct = col_terms(r, c.dx);
+        float p2[PPT];
+        uint64_t on[PPT], any = 0;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            p2[k] = power2(ct, r.p1.y, c.dy[k]);
+            on[k] = lanes(p2[k] >= r.p1.w);
+            if (!FULL) on[k] &= lanes(pos < my_n[k]);
+            any |= on[k];
+        }
+        if (any == 0) continue;
+        if (CLAMPS && may_clamp(r.p1.z, amax))
+            bwd_entry<PPT, true, DET>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
+        else
+            bwd_entry<PPT, false, DET>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
     }
 }
 
 template <int PPT, int GSR_BATCH, bool DET, bool MIXED>
-__global__ __launch_bounds__(64) void k_raster_bwd(RasterArgs a)
+__global__ __launch_bounds__(64, PPT <= 4 ? 5 : 3) void k_raster_bwd(RasterArgs a)
 {
     __shared__ LdsRec rec[GSR_BATCH];
     const TileCtx<PPT> c = tile_ctx<PPT>(a);
@@ -606,16 +693,16 @@ __global__ __launch_bounds__(64) void k_raster_bwd(RasterArgs a)
     // reads the flag, has completed before this kernel starts)
     if (blockIdx.x == 0 && threadIdx.x == 0) a.counters->grad_dirty = 1u;
     const int lane = threadIdx.x;
-    if (a.counters->overflow) {
+    if (uniform((int)a.counters->overflow)) {
         view_done(a, c.tile, lane);
         return;
     }
-    const uint2 range = a.ranges[c.tile];
+    const uint2 range = tile_range(a, c.tile);
     const float amax = a.cfg.alpha_max;
 
     float T[PPT], Tf[PPT], gsk[PPT], g0[PPT], g1[PPT], g2[PPT], dy2[PPT];
     uint32_t my_n[PPT];
-    uint32_t lane_max = 0;
+    uint32_t lane_max = 0, lane_min = 0xffffffffu;
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         Tf[k] = 1.0f;
@@ -635,46 +722,42 @@ __global__ __launch_bounds__(64) void k_raster_bwd(RasterArgs a)
         // g . (colour behind) + dL/dT_final T_final, maintained incrementally
         gsk[k] = __builtin_fmaf(gT, Tf[k], Tf[k] * (g0[k] * a.cfg.bg0 + g1[k] * a.cfg.bg1 + g2[k] * a.cfg.bg2));
         lane_max = max(lane_max, my_n[k]);
+        lane_min = min(lane_min, my_n[k]);
     }
-    for (int off = 32; off > 0; off >>= 1) lane_max = max(lane_max, (uint32_t)__shfl_xor((int)lane_max, off, 64));
-    const uint32_t end = range.x + min(lane_max, range.y - range.x);
+    for (int off = 32; off > 0; off >>= 1) {
+        lane_max = max(lane_max, (uint32_t)__shfl_xor((int)lane_max, off, 64));
+        lane_min = min(lane_min, (uint32_t)__shfl_xor((int)lane_min, off, 64));
+    }
+    // positions below this are blended by every pixel (0 where the tile
+    // reaches outside the view)
+    const uint32_t full = (uint32_t)uniform((int)lane_min);
+    const uint32_t end = range.x + min((uint32_t)uniform((int)lane_max), range.y - range.x);
 
-    PendingField pend{false, 0u, 0.0f};
+    PendingField pend{0, 0, 0.0f};
     for (uint32_t hi_ = end; hi_ > range.x;) {
         const uint32_t lo_ = hi_ - range.x > (uint32_t)GSR_BATCH ? hi_ - GSR_BATCH : range.x;
         const int cnt = (int)(hi_ - lo_);
+        bool may = false;
 #pragma unroll
         for (int r = 0; r < GSR_BATCH / 64; ++r) {
             const int t = lane + 64 * r;
-            if (t < cnt) stage_record<MIXED>(a, a.vals[hi_ - 1 - t], c.xc, c.yc, rec[t]);
+            if (t < cnt) may |= !(stage_record<MIXED>(a, a.vals[hi_ - 1 - t], c.xc, c.yc, rec[t]) < amax);
         }
+        const bool clamps = lanes(may) != 0;
         __syncthreads();
-        for (int e = 0; e < cnt; ++e) {
-            const uint32_t pos = hi_ - 1 - (uint32_t)e - range.x;
-            const LdsRec r = rec[e];
-            const ColTerms ct = col_terms(r, c.dx);
-            float p2[PPT];
-            bool on[PPT], any = false;
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                p2[k] = power2(ct, r.p1.y, c.dy[k]);
-                on[k] = (pos < my_n[k]) & (p2[k] >= r.p1.w);
-                any |= on[k];
-            }
-            if (!__any(any)) continue;
-            // alpha = o G <= o: only an entry with o >= alpha_max can clamp,
-            // a test uniform over the wave
-            if (may_clamp(r.p1.z, amax))
-                bwd_entry<PPT, true, DET>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
-            else
-                bwd_entry<PPT, false, DET>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
-        }
+        const uint32_t top = hi_ - 1 - range.x;
+        if (clamps)
+            bwd_batch<PPT, true, false, DET>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
+        else if (top < full)
+            bwd_batch<PPT, false, true, DET>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
+        else
+            bwd_batch<PPT, false, false, DET>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
         __syncthreads();
         hi_ = lo_;
     }
-    if (pend.have) {  // the last reduced entry's ninth field, alone
+    if (uniform(pend.have)) {  // the last reduced entry's ninth field, alone
         const float w = wave_sum_pair(pend.w, 0.0f);
-        if (lane == 1) add_field<DET>(a, pend.slot, 8, w);
+        if (lane == 1) add_field<DET>(a, (uint32_t)pend.slot, 8, w);
     }
     view_done(a, c.tile, lane);
 }
