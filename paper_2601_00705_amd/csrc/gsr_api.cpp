@@ -259,7 +259,7 @@ extern "C" gsr_status gsr_plan_create(int64_t n, int32_t n_views, const gsr_came
     p->off_seg = take(sizeof(unsigned long long) * pair_capacity);
     p->off_ranges = take(sizeof(uint2) * tiles);
     p->off_order = take(sizeof(uint32_t) * tiles);
-    p->off_buckets = take(sizeof(uint32_t) * 66);
+    p->off_buckets = take(sizeof(uint32_t) * 64);
     p->off_fwd_queue = take(sizeof(uint32_t));
     p->off_cnt = take(sizeof(uint32_t) * (size_t)p->chunks * (size_t)tiles);
     p->mask_words = (n + 63) / 64;
@@ -459,7 +459,6 @@ extern "C" gsr_status gsr_bin(gsr_plan* plan, void* stream)
     g.seg = b.seg;
     g.keys = at<unsigned long long>(plan, plan->off_keys);
     g.vals = at<uint32_t>(plan, plan->off_vals);
-    g.queue = r.buckets + 64;
     g.n = plan->n;
     hipError_t e;
     {
@@ -474,7 +473,7 @@ extern "C" gsr_status gsr_bin(gsr_plan* plan, void* stream)
     if (e != hipSuccess) return hip_fail(e, "gsr_bin: order");
     {
         Timed t(plan, GSR_T_BIN_SORT, s);
-        e = launch_seg_sort(g, plan->total_tiles, plan->capacity, s, plan->side, plan->fork_ev, plan->join_ev);
+        e = launch_seg_sort(g, plan->total_tiles, s);
     }
     return e == hipSuccess ? GSR_OK : hip_fail(e, "gsr_bin: sort");
 }

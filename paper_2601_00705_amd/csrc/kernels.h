@@ -52,7 +52,6 @@ struct SegArgs {
     unsigned long long* seg;   // [capacity]: emitted keys, sorted in place per tile (scratch)
     unsigned long long* keys;  // [capacity]: sorted (tile << 32 | depth bits)
     uint32_t* vals;            // [capacity]: sorted slots
-    uint32_t* queue;           // [1]: next list of the short class (zeroed by the ordering)
     int64_t n;
 };
 
@@ -61,7 +60,7 @@ struct RangeArgs {
     const uint2* ranges;
     int32_t total_tiles;
     uint32_t* order;           // [tiles]: tiles by pair count, descending
-    uint32_t* buckets;         // [66]: per log2-bucket counts, cursors, then the sort queue head
+    uint32_t* buckets;         // [64]: per log2-bucket counts, then cursors
 };
 
 struct RasterArgs {
@@ -289,12 +288,13 @@ struct FrameArgs {
 #endif
 #define GSR_LIVE_STRIDE 64          // uint32 between two views' live counters (one 256-byte line each)
 #define GSR_XCDS 8                  // accelerator dies; workgroups are dealt to them in turn
-#define GSR_SEG_SMALL_THREADS 256   // segments below GSR_SEG_SMALL_ITEMS keys: 256-thread blocks
-#define GSR_SEG_SMALL_ITEMS 2048
-#define GSR_SEG_THREADS 512
-#define GSR_SEG_ITEMS 8192          // segments below this size are sorted in LDS by 512-thread blocks
-#define GSR_SEG_LONG_THREADS 1024   // longer segments: one 1024-thread block each
-#define GSR_SEG_LONG_ITEMS 16384    // ... holding this many keys in LDS
+#ifndef GSR_SEG_THREADS
+#define GSR_SEG_THREADS 256         // threads of a sorting block
+#endif
+#define GSR_SEG_WAVES 5             // resident waves per SIMD (the LDS of five blocks of 256 threads)
+#define GSR_SEG_PER_THREAD 8        // keys per thread: a block sorts 8 x threads keys at once
+#define GSR_SEG_COARSE 1024         // linear depth bins that measure a list's depth distribution
+#define GSR_SEG_CROWDED 32          // mean bin-mates of a key above which the digits are sorted instead
 #define GSR_FWD_LONG 4096           // least list length of a tile composited in parts (power of 2)
 #define GSR_FWD_WAVES 5120          // resident compositing waves (256 CUs x 4 SIMDs x 5)
 #ifndef GSR_FWD_SPLIT
@@ -307,8 +307,7 @@ hipError_t launch_project(const ProjectArgs& a, int sh_degree, hipStream_t s);
 // the largest tile count of one view
 hipError_t launch_bin(const BinArgs& a, int max_tiles_view, hipStream_t s);
 hipError_t launch_order(const RangeArgs& a, hipStream_t s);
-hipError_t launch_seg_sort(const SegArgs& a, int total_tiles, int64_t capacity, hipStream_t s, hipStream_t side,
-                           hipEvent_t fork, hipEvent_t join);
+hipError_t launch_seg_sort(const SegArgs& a, int total_tiles, hipStream_t s);
 hipError_t launch_raster_fwd(const RasterArgs& a, int total_tiles, int tile_px, int batch, hipStream_t s,
                              hipStream_t side, hipEvent_t fork, hipEvent_t join);
 hipError_t launch_clear_grad2d(const RasterArgs& a, hipStream_t s);

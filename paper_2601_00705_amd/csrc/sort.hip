@@ -1,28 +1,36 @@
 // sort.hip -- per-tile ordering of the emitted pairs, and the tiles' order.
 //
-// k_seg_sort   one block per tile (longest first): sorts the
-//              segment's unique 64-bit keys (depth bits << 32 | Gaussian
-//              index) ascending with a stable LSD radix sort of 8-bit digits,
-//              skipping every digit that is the same for all keys of the
-//              segment.  In LDS the depth digits go first and the runs of
-//              equal depth are then put in index order by odd-even
-//              transposition (falling back to every digit when a run does
-//              not settle in 8 rounds).  Then it writes the final pairs: key (tile << 32 | depth
-//              bits), value slot = view * n + index.  Segments of up to
-//              the block's LDS capacity are sorted in LDS; longer ones in
-//              chunks of that size, then merged pairwise through global
-//              memory.
+// k_seg_sort   one block per tile (longest first): sorts the segment's unique
+//              64-bit keys (depth bits << 32 | Gaussian index) ascending and
+//              writes the final pairs: key (tile << 32 | depth bits), value
+//              slot = view * n + index.
 // k_order_*    processing order of the tiles: descending pair count, bucketed
 //              by floor(log2(count)), for the segment sort and compositing.
 //
-// Ranking inside the block is stable: items are ranked in index order (wave,
-// round, lane) with wave-private digit counters; equal digits inside a round
-// are found with 8 ballots.
+// A list is placed, not ranked digit by digit: a histogram of its depth bits
+// over GSR_SEG_COARSE linear bins gives its depth distribution, every coarse
+// bin of c keys is cut into c fine bins, and a key's position is its fine
+// bin's start (an LDS atomic and a scan) plus the smaller keys of its bin,
+// one or two on average whatever surfaces the depths lie on.  The keys are
+// unique, so no step needs to be stable.  Lists of more than 8 keys a thread
+// are first spread over runs of whole coarse bins (one pass through memory)
+// and these sorted one after another with the bins already known.  Where
+// depths coincide (a key has more than GSR_SEG_CROWDED bin-mates on average)
+// the keys are sorted by their digits instead, and runs that cannot be cut
+// by depth are merged.
+//
+// The kernel is bound by LDS traffic and, for the long lists, by the passes
+// over memory (20 bytes a key, 24 more for a long list's three reads less
+// what the caches hold).  It replaced four or more 8-bit digit passes of
+// eight ballots each over three classes of lists on two streams: 4.8M pairs
+// in lists of 290 (five 1200x680 views of 500k Gaussians) 431 -> 78 us, 41M
+// pairs in lists of 1500 to 18500 (ten such views of 1M) 750 -> 380 us, 265M
+// pairs in lists of 2800 to 48600 (36 views of 3M) about 5300 -> 2650 us,
+// 194k pairs in lists of 150 76 -> 8 us.  Measured and worse: 512 threads and
+// 4096 keys a block, 4 keys a thread (more, smaller runs of the long lists:
+// 4930 us), 2048 coarse bins (2870 us), pairs written from the threads that
+// ranked them instead of in order through LDS (3750 us).
 #include "kernels.h"
-
-#ifndef GSR_SORT_SMALL_MAIN
-#define GSR_SORT_SMALL_MAIN 512  // small-class blocks also launched on the main stream (0: none)
-#endif
 
 namespace gsr {
 
@@ -44,15 +52,28 @@ __device__ __forceinline__ unsigned long long match_digit(uint32_t d, bool valid
     return ((unsigned long long)hi << 32) | lo;
 }
 
-template <int WAVES, int ITEMS>
+template <int WAVES>
 struct SegLds {
-    // the digit scans give one thread to each of the 256 digits
-    static_assert(WAVES * 64 >= 256, "a sorting block needs at least 256 threads");
-    unsigned long long sk[ITEMS];          // keys in digit order (LDS path)
-    uint32_t wcnt[WAVES][256];             // per-wave digit counters, then wave offsets
-    uint32_t dstart[256];                  // block-local start of each digit
-    uint32_t wsum[4];
-    unsigned long long red[2][WAVES];
+    static constexpr int THREADS = WAVES * 64;
+    static constexpr int ITEMS = THREADS * GSR_SEG_PER_THREAD;  // keys sorted at once
+    static_assert(GSR_SEG_COARSE % THREADS == 0, "a thread scans the same number of coarse bins");
+    // the digit scans of the radix sort give one thread to each digit
+    static_assert(THREADS >= 256, "a sorting block needs at least 256 threads");
+    union {
+        unsigned long long sk[ITEMS];        // keys in fine-bin (digit) order
+        uint32_t coarse[GSR_SEG_COARSE + 1]; // coarse counts, then starts (before sk is filled)
+    };
+    union {
+        uint32_t fine[ITEMS + 1];            // fine counts, then starts
+        struct {
+            uint32_t wcnt[WAVES][256];       // radix sort: per-wave digit counters, then wave offsets
+            uint32_t dstart[256];            // and the block-local start of each digit
+        };
+    };
+    uint32_t starts[GSR_SEG_COARSE + 1];     // a long list's coarse bins: counts, then starts
+    uint32_t wsum[WAVES], wsum2[WAVES];
+    uint32_t red[2][WAVES];
+    unsigned long long red64[2][WAVES];
 };
 
 // Stable ranking of the block's items by digit (key >> shift) & 255.  Item
@@ -60,9 +81,9 @@ struct SegLds {
 // pos[r] is its position in digit order (digit-major, index order within a
 // digit) or ~0 for an item past m, and L.dstart[] holds the first position
 // of each digit.
-template <int WAVES, int ITEMS, int MAXR>
+template <int WAVES, int MAXR>
 __device__ __forceinline__ void rank_items(const unsigned long long* key, int R, int m, int shift, uint32_t* pos,
-                                           SegLds<WAVES, ITEMS>& L)
+                                           SegLds<WAVES>& L)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     for (int k = tid; k < WAVES * 256; k += WAVES * 64) (&L.wcnt[0][0])[k] = 0u;
@@ -116,30 +137,6 @@ __device__ __forceinline__ void rank_items(const unsigned long long* key, int R,
     }
 }
 
-// OR and AND of the block's keys (identity for no key)
-template <int WAVES, int ITEMS>
-__device__ __forceinline__ void block_or_and(unsigned long long o, unsigned long long a, SegLds<WAVES, ITEMS>& L,
-                                             unsigned long long& bor, unsigned long long& band)
-{
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    for (int off = 32; off > 0; off >>= 1) {
-        o |= __shfl_xor(o, off, 64);
-        a &= __shfl_xor(a, off, 64);
-    }
-    if (lane == 0) {
-        L.red[0][w] = o;
-        L.red[1][w] = a;
-    }
-    __syncthreads();
-    bor = 0ull;
-    band = ~0ull;
-    for (int k = 0; k < WAVES; ++k) {
-        bor |= L.red[0][k];
-        band &= L.red[1][k];
-    }
-    __syncthreads();
-}
-
 __device__ __forceinline__ void write_pair(const SegArgs& a, uint32_t at, unsigned long long k, unsigned long long tile,
                                            uint32_t vbase)
 {
@@ -147,15 +144,12 @@ __device__ __forceinline__ void write_pair(const SegArgs& a, uint32_t at, unsign
     a.vals[at] = vbase + (uint32_t)k;
 }
 
-// Sorts the m <= ITEMS keys src[0, m) with the whole block in LDS; on return
-// key[r] of thread (w, lane) holds the key of sorted position
-// w * R * 64 + r * 64 + lane (R = ceil(m / THREADS)) when that is below m.
-template <int WAVES, int ITEMS>
-__device__ void lds_sort(const unsigned long long* src, int m, unsigned long long (&key)[ITEMS / (WAVES * 64)],
-                         SegLds<WAVES, ITEMS>& L)
+// Stable LSD radix sort of the block's keys (item (r, lane) of wave w at
+// index w * R * 64 + r * 64 + lane) by the digits in which they differ.
+template <int WAVES>
+__device__ __forceinline__ void radix_sort(unsigned long long (&key)[GSR_SEG_PER_THREAD], int m, SegLds<WAVES>& L)
 {
-    constexpr int THREADS = WAVES * 64;
-    constexpr int MAXR = ITEMS / THREADS;
+    constexpr int THREADS = WAVES * 64, MAXR = GSR_SEG_PER_THREAD;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int R = (m + THREADS - 1) / THREADS;
     uint32_t pos[MAXR];
@@ -163,93 +157,249 @@ __device__ void lds_sort(const unsigned long long* src, int m, unsigned long lon
 #pragma unroll
     for (int r = 0; r < MAXR; ++r) {
         if (r >= R) break;
-        const int li = w * R * 64 + r * 64 + lane;
-        key[r] = li < m ? src[li] : 0ull;
-        if (li < m) {
+        if (w * R * 64 + r * 64 + lane < m) {
             o |= key[r];
             an &= key[r];
         }
     }
-    unsigned long long bor, band;
-    block_or_and(o, an, L, bor, band);
+    for (int off = 32; off > 0; off >>= 1) {
+        o |= __shfl_xor(o, off, 64);
+        an &= __shfl_xor(an, off, 64);
+    }
+    if (lane == 0) {
+        L.red64[0][w] = o;
+        L.red64[1][w] = an;
+    }
+    __syncthreads();
+    unsigned long long bor = 0ull, band = ~0ull;
+    for (int k = 0; k < WAVES; ++k) {
+        bor |= L.red64[0][k];
+        band &= L.red64[1][k];
+    }
     const unsigned long long diff = bor ^ band;
-    // depth digits first.  Keys that share a depth then stand in runs in
-    // emission order; odd-even transposition inside those runs puts them in
-    // index order (a few rounds: runs are short).  Runs that do not settle
-    // within 8 rounds fall back to sorting every digit, LSD from the index.
-    bool sorted = false, in_lds = false;
-    for (int d = 4; d < 8; ++d) {
+    for (int d = 0; d < 8; ++d) {
         if (((diff >> (8 * d)) & 255ull) == 0ull) continue;
-        rank_items<WAVES, ITEMS, MAXR>(key, R, m, 8 * d, pos, L);
+        __syncthreads();
+        rank_items<WAVES, MAXR>(key, R, m, 8 * d, pos, L);
 #pragma unroll
         for (int r = 0; r < MAXR; ++r) {
             if (r >= R) break;
             if (pos[r] != 0xffffffffu) L.sk[pos[r]] = key[r];
         }
         __syncthreads();
-        in_lds = true;
 #pragma unroll
         for (int r = 0; r < MAXR; ++r) {
             if (r >= R) break;
             const int li = w * R * 64 + r * 64 + lane;
             if (li < m) key[r] = L.sk[li];
         }
-        __syncthreads();
     }
-    if ((diff & 0xffffffffull) == 0ull) {
-        sorted = true;  // a single key
-    } else if (diff >> 32) {
-        if (!in_lds) {
+    __syncthreads();
+}
+
+// The linear map of depth bits (offset from the least, at most range) to
+// GSR_SEG_COARSE coarse bins: the product's high word is the bin, its low
+// word the place inside the bin.  mult = floor(bins 2^32 / (range + 1)), and
+// range / (range + 1) <= 1 - 2^-32, so the bin is below GSR_SEG_COARSE
+// whichever way the quotient rounds.
+__device__ __forceinline__ unsigned long long coarse_mult(uint32_t range)
+{
+    return (unsigned long long)((double)GSR_SEG_COARSE * 4294967296.0 / ((double)range + 1.0));
+}
+
+// least and largest depth bits over the block
+template <int WAVES>
+__device__ __forceinline__ void block_min_max(uint32_t& lo, uint32_t& hi, SegLds<WAVES>& L)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+    }
+    if (lane == 0) {
+        L.red[0][w] = lo;
+        L.red[1][w] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) {
+        lo = min(lo, L.red[0][k]);
+        hi = max(hi, L.red[1][k]);
+    }
+}
+
+// Exclusive prefix of cnt[0, K THREADS) in place, K counters to a thread; the
+// return value is the sum over all counters of f(counter), saturating.  Ends
+// with a barrier.
+template <int WAVES, int MAXK, class F>
+__device__ __forceinline__ uint32_t scan_bins(uint32_t* cnt, int K, SegLds<WAVES>& L, F&& f, bool want_max)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    uint32_t c[MAXK], sum = 0, q = 0;
+#pragma unroll
+    for (int k = 0; k < MAXK; ++k) {
+        if (k >= K) break;
+        c[k] = cnt[tid * K + k];
+        sum += c[k];
+        q = want_max ? max(q, c[k]) : q + f(c[k]);
+    }
+    uint32_t incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += y;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t y = (uint32_t)__shfl_xor((int)q, off, 64);
+        q = want_max ? max(q, y) : q + y;
+    }
+    if (lane == 63) {
+        L.wsum[w] = incl;
+        L.wsum2[w] = q;
+    }
+    __syncthreads();
+    uint32_t run = incl - sum;
+    q = 0;
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) {
+        run += k < w ? L.wsum[k] : 0u;
+        q = want_max ? max(q, L.wsum2[k]) : q + L.wsum2[k];
+    }
+#pragma unroll
+    for (int k = 0; k < MAXK; ++k) {
+        if (k >= K) break;
+        cnt[tid * K + k] = run;
+        run += c[k];
+    }
+    __syncthreads();
+    return q;
+}
+
+// A list's (chunk's) coarse bins, as the fine bins need them.
+struct Coarse {
+    uint32_t lo;              // least depth bits
+    unsigned long long mult;  // coarse_mult of their range
+};
+
+// Sorts the m <= ITEMS unique keys src[0, m) with the whole block; on return
+// (after a barrier) key[r] of thread (w, lane) holds the key of sorted
+// position w * R * 64 + r * 64 + lane (R = ceil(m / THREADS)) when that is
+// below m.  One pass places every key in one of m bins that follow the
+// list's own depth distribution, about one key to a bin; a key's position is
+// then its bin's start plus the smaller keys of its bin.  The distribution
+// is measured on the keys, or (known) it is that of the long list they are
+// a part of: the bins of L.starts, src starting at position `done`.
+template <int WAVES>
+__device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, bool known, Coarse in_list, uint32_t done,
+                                         unsigned long long (&key)[GSR_SEG_PER_THREAD], SegLds<WAVES>& L)
+{
+    constexpr int THREADS = WAVES * 64, MAXR = GSR_SEG_PER_THREAD, NC = GSR_SEG_COARSE / THREADS;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int R = (m + THREADS - 1) / THREADS;
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+        if (r >= R) break;
+        const int li = w * R * 64 + r * 64 + lane;
+        key[r] = li < m ? src[li] : ~0ull;
+    }
+    uint32_t bin[MAXR], rank[MAXR];
+    {
+#pragma unroll
+        for (int r = 0; r < MAXR; ++r) {
+            if (r >= R) break;
+            L.fine[tid + r * THREADS] = 0u;
+        }
+        // coarse bin b of c keys is cut into c fine bins, numbered from its
+        // start
+        if (known) {
+            __syncthreads();
 #pragma unroll
             for (int r = 0; r < MAXR; ++r) {
                 if (r >= R) break;
                 const int li = w * R * 64 + r * 64 + lane;
-                if (li < m) L.sk[li] = key[r];
-            }
-            __syncthreads();
-        }
-        for (int round = 0; round < 8 && !sorted; ++round) {
-            bool swapped = false;
-            for (int par = 0; par < 2; ++par) {
-                for (int i = par + 2 * tid; i + 1 < m; i += 2 * THREADS) {
-                    const unsigned long long x = L.sk[i], y = L.sk[i + 1];
-                    if ((x >> 32) == (y >> 32) && x > y) {
-                        L.sk[i] = y;
-                        L.sk[i + 1] = x;
-                        swapped = true;
-                    }
+                if (li < m) {
+                    const unsigned long long p = (unsigned long long)((uint32_t)(key[r] >> 32) - in_list.lo) * in_list.mult;
+                    const uint32_t b = (uint32_t)(p >> 32), s = L.starts[b], e = L.starts[b + 1];
+                    bin[r] = s - done + __umulhi((uint32_t)p, e - s);
+                    rank[r] = atomicAdd(&L.fine[bin[r]], 1u);
                 }
-                __syncthreads();
             }
-            sorted = __syncthreads_or(swapped) == 0;
-        }
-#pragma unroll
-        for (int r = 0; r < MAXR; ++r) {
-            if (r >= R) break;
-            const int li = w * R * 64 + r * 64 + lane;
-            if (li < m) key[r] = L.sk[li];
-        }
-        __syncthreads();
-    }
-    if (!sorted) {
-        for (int d = 0; d < 8; ++d) {
-            if (((diff >> (8 * d)) & 255ull) == 0ull) continue;
-            rank_items<WAVES, ITEMS, MAXR>(key, R, m, 8 * d, pos, L);
+        } else {
+            uint32_t lo = 0xffffffffu, hi = 0u;
 #pragma unroll
             for (int r = 0; r < MAXR; ++r) {
                 if (r >= R) break;
-                if (pos[r] != 0xffffffffu) L.sk[pos[r]] = key[r];
+                const int li = w * R * 64 + r * 64 + lane;
+                if (li < m) {
+                    lo = min(lo, (uint32_t)(key[r] >> 32));
+                    hi = max(hi, (uint32_t)(key[r] >> 32));
+                }
             }
+#pragma unroll
+            for (int k = 0; k < NC; ++k) L.coarse[tid + k * THREADS] = 0u;
+            block_min_max<WAVES>(lo, hi, L);
+            const unsigned long long mult = coarse_mult(hi - lo);
+#pragma unroll
+            for (int r = 0; r < MAXR; ++r) {
+                if (r >= R) break;
+                const int li = w * R * 64 + r * 64 + lane;
+                if (li < m) atomicAdd(&L.coarse[((unsigned long long)((uint32_t)(key[r] >> 32) - lo) * mult) >> 32], 1u);
+            }
+            __syncthreads();
+            scan_bins<WAVES, NC>(L.coarse, NC, L, [](uint32_t) { return 0u; }, true);
+            if (tid == 0) L.coarse[GSR_SEG_COARSE] = (uint32_t)m;
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < MAXR; ++r) {
                 if (r >= R) break;
                 const int li = w * R * 64 + r * 64 + lane;
-                if (li < m) key[r] = L.sk[li];
+                if (li < m) {
+                    const unsigned long long p = (unsigned long long)((uint32_t)(key[r] >> 32) - lo) * mult;
+                    const uint32_t b = (uint32_t)(p >> 32), s = L.coarse[b], e = L.coarse[b + 1];
+                    bin[r] = s + __umulhi((uint32_t)p, e - s);
+                    rank[r] = atomicAdd(&L.fine[bin[r]], 1u);
+                }
             }
-            __syncthreads();
+        }
+        __syncthreads();
+        const uint32_t pairs = scan_bins<WAVES, MAXR>(L.fine, R, L, [](uint32_t c) { return c * c; }, false);
+        if (pairs > GSR_SEG_CROWDED * (uint32_t)m) {
+            // too many keys share (nearly) one depth: compared with each
+            // other they would cost more than the digits do
+            radix_sort<WAVES>(key, m, L);
+            return;
         }
     }
+    if (tid == 0) L.fine[R * THREADS] = (uint32_t)m;
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+        if (r >= R) break;
+        if (w * R * 64 + r * 64 + lane < m) L.sk[L.fine[bin[r]] + rank[r]] = key[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+        if (r >= R) break;
+        if (w * R * 64 + r * 64 + lane < m) {
+            const uint32_t s = L.fine[bin[r]], e = L.fine[bin[r] + 1];
+            rank[r] = s;
+            if (e - s > 1u)
+                for (uint32_t j = s; j < e; ++j) rank[r] += L.sk[j] < key[r] ? 1u : 0u;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+        if (r >= R) break;
+        if (w * R * 64 + r * 64 + lane < m) L.sk[rank[r]] = key[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+        if (r >= R) break;
+        const int li = w * R * 64 + r * 64 + lane;
+        if (li < m) key[r] = L.sk[li];
+    }
+    __syncthreads();
 }
 
 // Merges the sorted runs A[0, na) and B[0, nb) (unique keys) with the whole
@@ -278,60 +428,126 @@ __device__ __forceinline__ void merge_runs(const unsigned long long* A, int na, 
     }
 }
 
-// Sorts the segment of one tile with the whole block (WAVES * 64 threads,
-// ITEMS keys fit in LDS).  A longer segment is cut into chunks of ITEMS
-// keys, each sorted in LDS, and the sorted chunks are merged pairwise
-// (merge path) through global memory, ping-ponging between the segment's
-// emission buffer and its output key array; the last merge reads the
-// emission buffer and writes the final pairs.
-template <int WAVES, int ITEMS, bool CHUNKED>
-__device__ void sort_segment(const SegArgs& a, uint32_t tile, uint2 rg, SegLds<WAVES, ITEMS>& L)
+// f(key) for the keys src[0, m), the block's threads taking them in turn; eight
+// loads are in flight per thread (a list's passes over memory are otherwise
+// chains of one load's latency per THREADS keys).
+template <int THREADS, class F>
+__device__ __forceinline__ void for_keys(const unsigned long long* src, int m, F&& f)
 {
-    constexpr int THREADS = WAVES * 64;
-    constexpr int MAXR = ITEMS / THREADS;
+    constexpr int K = 8;
+    int i = threadIdx.x;
+    for (; i + (K - 1) * THREADS < m; i += K * THREADS) {
+        unsigned long long k[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) k[j] = src[i + j * THREADS];
+#pragma unroll
+        for (int j = 0; j < K; ++j) f(k[j]);
+    }
+    for (; i < m; i += THREADS) f(src[i]);
+}
+
+// Sorts the segment of one tile with the whole block.  A list of up to ITEMS
+// keys is sorted in LDS.  A longer one is first spread over its coarse depth
+// bins (emission buffer to output key array, the order inside a bin being
+// arbitrary); whole bins are then taken together up to ITEMS keys at a time
+// and sorted in LDS, in place.  Where more than ITEMS keys share one coarse
+// bin, chunks of ITEMS keys are sorted as they stand and merged pairwise
+// (merge path) through global memory, ping-ponging between the two buffers;
+// the last merge reads the emission buffer and writes the final pairs.
+template <int WAVES>
+__device__ __forceinline__ void sort_segment(const SegArgs& a, uint32_t tile, uint2 rg, SegLds<WAVES>& L)
+{
+    constexpr int THREADS = WAVES * 64, MAXR = GSR_SEG_PER_THREAD, ITEMS = SegLds<WAVES>::ITEMS;
+    constexpr int NC = GSR_SEG_COARSE / THREADS;
     const int m = (int)(rg.y - rg.x);
     const int v = view_of_tile(a.views, (int)tile);
     const uint32_t vbase = (uint32_t)((int64_t)v * a.n);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    unsigned long long key[MAXR];
-
-    if (m <= ITEMS) {
-        lds_sort<WAVES, ITEMS>(a.seg + rg.x, m, key, L);
-        const int R = (m + THREADS - 1) / THREADS;
-#pragma unroll
-        for (int r = 0; r < MAXR; ++r) {
-            if (r >= R) break;
-            const int li = w * R * 64 + r * 64 + lane;
-            if (li < m) write_pair(a, rg.x + (uint32_t)li, key[r], tile, vbase);
-        }
-        return;
-    }
-    if (!CHUNKED) return;  // not reached: the class's lists fit in LDS
-
-    unsigned long long* bufA = a.seg + rg.x;
-    unsigned long long* bufB = a.keys + rg.x;  // output keys double as scratch
-    const int chunks = (m + ITEMS - 1) / ITEMS;
+    unsigned long long* const bufA = a.seg + rg.x;
+    unsigned long long* const bufB = a.keys + rg.x;  // output keys double as scratch
+    const unsigned long long* src = bufA;
+    unsigned long long* cur = nullptr;  // where sorted chunks wait for merging
+    Coarse bins{0u, 0ull};
+    uint32_t per_start = 0u;
     int passes = 0;
-    while ((1 << passes) < chunks) ++passes;
-    // the sorted chunks go where the last merge will read from bufA
-    unsigned long long* cur = (passes & 1) ? bufA : bufB;
-    for (int cb = 0; cb < m; cb += ITEMS) {
-        const int cm = min(ITEMS, m - cb);
-        lds_sort<WAVES, ITEMS>(bufA + cb, cm, key, L);
+    if (m > ITEMS) {
+        uint32_t lo = 0xffffffffu, hi = 0u;
+        for_keys<THREADS>(bufA, m, [&](unsigned long long k) {
+            lo = min(lo, (uint32_t)(k >> 32));
+            hi = max(hi, (uint32_t)(k >> 32));
+        });
+#pragma unroll
+        for (int k = 0; k < NC; ++k) L.starts[tid + k * THREADS] = 0u;
+        block_min_max<WAVES>(lo, hi, L);
+        const unsigned long long mult = coarse_mult(hi - lo);
+        for_keys<THREADS>(bufA, m, [&](unsigned long long k) {
+            atomicAdd(&L.starts[((unsigned long long)((uint32_t)(k >> 32) - lo) * mult) >> 32], 1u);
+        });
+        __syncthreads();
+        const uint32_t most = scan_bins<WAVES, NC>(L.starts, NC, L, [](uint32_t) { return 0u; }, true);
+        // (the chunks' cursors need a place each, and tiny chunks do not pay)
+        if (most <= (uint32_t)(ITEMS - ITEMS / 8) && (uint32_t)m / ((uint32_t)ITEMS - most) < (uint32_t)ITEMS) {
+            // chunk of a coarse bin, by its start: the starts of one chunk's
+            // bins differ by at most ITEMS - most, so it holds at most ITEMS
+            per_start = 0xffffffffu / ((uint32_t)ITEMS - most);
+            // the chunks' cursors, in the fine bins' place
+            if (tid == 0) L.starts[GSR_SEG_COARSE] = (uint32_t)m;
+            for (int b = tid; b < GSR_SEG_COARSE; b += THREADS) {
+                const uint32_t c = __umulhi(L.starts[b], per_start);
+                if (b == 0 || __umulhi(L.starts[b - 1], per_start) != c) L.fine[c] = L.starts[b];
+            }
+            __syncthreads();
+            for_keys<THREADS>(bufA, m, [&](unsigned long long k) {
+                const uint32_t b = (uint32_t)(((unsigned long long)((uint32_t)(k >> 32) - lo) * mult) >> 32);
+                bufB[atomicAdd(&L.fine[__umulhi(L.starts[b], per_start)], 1u)] = k;
+            });
+            __syncthreads();  // the block's own writes are visible to it
+            src = bufB;
+            bins = Coarse{lo, mult};
+        } else {
+            while (((long long)ITEMS << passes) < m) ++passes;
+            // where the last merge will read from bufA
+            cur = (passes & 1) ? bufA : bufB;
+        }
+    }
+    for (int done = 0; done < m;) {
+        int cm = m - done;
+        if (m > ITEMS) {
+            cm = min(cm, ITEMS);
+            if (!cur) {
+                // up to the first bin of a later chunk
+                const uint32_t c = __umulhi((uint32_t)done, per_start);
+                int b0 = 0, b1 = GSR_SEG_COARSE;
+                while (b0 < b1) {
+                    const int mid = (b0 + b1) >> 1;
+                    if (__umulhi(L.starts[mid], per_start) > c) b1 = mid;
+                    else b0 = mid + 1;
+                }
+                cm = (int)L.starts[b0] - done;
+            }
+        }
+        unsigned long long key[MAXR];
+        lds_sort<WAVES>(src + done, cm, src != bufA, bins, (uint32_t)done, key, L);
         const int R = (cm + THREADS - 1) / THREADS;
 #pragma unroll
         for (int r = 0; r < MAXR; ++r) {
             if (r >= R) break;
             const int li = w * R * 64 + r * 64 + lane;
-            if (li < cm) cur[cb + li] = key[r];
+            if (li < cm) {
+                if (cur) cur[done + li] = key[r];
+                else write_pair(a, rg.x + (uint32_t)(done + li), key[r], tile, vbase);
+            }
         }
-        __syncthreads();
+        done += cm;
     }
-    for (int p = 1, width = ITEMS; p <= passes; ++p, width *= 2) {
+    if (!cur) return;
+    __syncthreads();
+    long long width = ITEMS;
+    for (int p = 1; p <= passes; ++p, width *= 2) {
         unsigned long long* nxt = cur == bufA ? bufB : bufA;
-        for (int a0 = 0; a0 < m; a0 += 2 * width) {
-            const int na = min(width, m - a0);
-            const int nb = max(0, min(width, m - a0 - width));
+        for (long long a0 = 0; a0 < m; a0 += 2 * width) {
+            const int na = (int)min(width, m - a0);
+            const int nb = (int)max(0ll, min(width, m - a0 - width));
             if (p == passes)
                 merge_runs<THREADS>(cur + a0, na, cur + a0 + na, nb, [&](int d, unsigned long long k) {
                     write_pair(a, rg.x + (uint32_t)(a0 + d), k, tile, vbase);
@@ -345,103 +561,25 @@ __device__ void sort_segment(const SegArgs& a, uint32_t tile, uint2 rg, SegLds<W
     }
 }
 
-// first position of the processing order whose tile has fewer than `below`
-// pairs (the order is grouped by floor(log2(count)), longest first, and
-// `below` is a power of two, so the predicate is monotone along it)
-__device__ __forceinline__ int first_below(const SegArgs& a, int total_tiles, uint32_t below)
+// One block per tile, in the processing order: the blocks of the longest
+// lists start first, and the empty tiles' blocks, which end the order, exit.
+__global__ __launch_bounds__(GSR_SEG_THREADS, GSR_SEG_WAVES) void k_seg_sort(SegArgs a)
 {
-    int lo = 0, hi = total_tiles;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const uint2 r = a.ranges[a.order[mid]];
-        if (r.y - r.x < below) hi = mid;
-        else lo = mid + 1;
-    }
-    return lo;
-}
-
-// Three classes of segments, each a contiguous stretch of the processing
-// order (longest first).  CLASS 2, lists of GSR_SEG_ITEMS keys or more, and
-// CLASS 1, from GSR_SEG_SMALL_ITEMS up to GSR_SEG_ITEMS: block b takes
-// position b and returns at once if that tile belongs to another class (the
-// middle class's blocks retire tile by tile, which lets the long class's
-// blocks in; persistent middle blocks measured slower where long lists are
-// many).  CLASS 0, below GSR_SEG_SMALL_ITEMS: persistent 256-thread blocks
-// take tiles from a work queue over their stretch (found by binary search),
-// so no block is spent on another class's tile; the small blocks keep more
-// short lists in flight per CU.
-template <int THREADS, int ITEMS, int CLASS>
-__global__ __launch_bounds__(THREADS) void k_seg_sort(SegArgs a, int total_tiles)
-{
-    __shared__ SegLds<THREADS / 64, ITEMS> L;
+    __shared__ SegLds<GSR_SEG_THREADS / 64> L;
     if (a.counters->overflow) return;
-    if (CLASS == 2) {
-        const uint32_t tile = a.order[blockIdx.x];
-        const uint2 rg = a.ranges[tile];
-        if (rg.y - rg.x < (uint32_t)GSR_SEG_ITEMS) return;
-        sort_segment<THREADS / 64, ITEMS, true>(a, tile, rg, L);
-        return;
-    }
-    if (CLASS == 1) {
-        const uint32_t tile = a.order[blockIdx.x];
-        const uint2 rg = a.ranges[tile];
-        const uint32_t m = rg.y - rg.x;
-        if (m < (uint32_t)GSR_SEG_SMALL_ITEMS || m >= (uint32_t)GSR_SEG_ITEMS) return;
-        sort_segment<THREADS / 64, ITEMS, false>(a, tile, rg, L);
-        return;
-    }
-    const int begin = first_below(a, total_tiles, GSR_SEG_SMALL_ITEMS);
-    const int end = total_tiles;
-    __shared__ int next;
-    for (;;) {
-        if (threadIdx.x == 0) next = begin + (int)atomicAdd(&a.queue[CLASS], 1u);
-        __syncthreads();
-        const int p = next;
-        __syncthreads();
-        if (p >= end) break;
-        const uint32_t tile = a.order[p];
-        const uint2 rg = a.ranges[tile];
-        if (rg.y == rg.x) break;  // empty tiles end the order
-        sort_segment<THREADS / 64, ITEMS, false>(a, tile, rg, L);
-    }
+    const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.order[blockIdx.x]);
+    const uint2 r = a.ranges[tile];
+    const uint2 rg = make_uint2((uint32_t)__builtin_amdgcn_readfirstlane((int)r.x),
+                                (uint32_t)__builtin_amdgcn_readfirstlane((int)r.y));
+    if (rg.y == rg.x) return;
+    sort_segment<GSR_SEG_THREADS / 64>(a, tile, rg, L);
 }
 
-// The long segments run on `side`, forked from `s` after the tile ranges,
-// followed there by the short ones; the middle class runs on `s`; `side` is
-// joined back before anything later on `s` (the fork and join are recorded
-// into a graph when `s` is captured).
-hipError_t launch_seg_sort(const SegArgs& a, int total_tiles, int64_t capacity, hipStream_t s, hipStream_t side,
-                           hipEvent_t fork, hipEvent_t join)
+hipError_t launch_seg_sort(const SegArgs& a, int total_tiles, hipStream_t s)
 {
     if (total_tiles == 0) return hipSuccess;
-    hipError_t e = hipEventRecord(fork, s);
-    if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
-    if (e != hipSuccess) return e;
-    // the long segments lead the processing order, and at most
-    // capacity / GSR_SEG_ITEMS of them fit in the pair buffer
-    const int64_t longs = capacity / GSR_SEG_ITEMS + 1;
-    const unsigned long_grid = (unsigned)(longs < total_tiles ? longs : total_tiles);
-    hipLaunchKernelGGL((k_seg_sort<GSR_SEG_LONG_THREADS, GSR_SEG_LONG_ITEMS, 2>), dim3(long_grid),
-                       dim3(GSR_SEG_LONG_THREADS), 0, side, a, total_tiles);
-    // the small class: four persistent blocks per CU (what their registers
-    // allow)
-    const unsigned small_grid = (unsigned)(total_tiles < 1024 ? total_tiles : 1024);
-    hipLaunchKernelGGL((k_seg_sort<GSR_SEG_SMALL_THREADS, GSR_SEG_SMALL_ITEMS, 0>), dim3(small_grid),
-                       dim3(GSR_SEG_SMALL_THREADS), 0, side, a, total_tiles);
-    hipLaunchKernelGGL((k_seg_sort<GSR_SEG_THREADS, GSR_SEG_ITEMS, 1>), dim3((unsigned)total_tiles),
-                       dim3(GSR_SEG_THREADS), 0, s, a, total_tiles);
-    // more persistent small-class blocks on `s` once the middle class is
-    // done: they take tiles from the same queue as those on `side`, so the
-    // stream that frees up first drains the short lists
-    if (GSR_SORT_SMALL_MAIN > 0) {
-        const unsigned g = (unsigned)(total_tiles < GSR_SORT_SMALL_MAIN ? total_tiles : GSR_SORT_SMALL_MAIN);
-        hipLaunchKernelGGL((k_seg_sort<GSR_SEG_SMALL_THREADS, GSR_SEG_SMALL_ITEMS, 0>), dim3(g),
-                           dim3(GSR_SEG_SMALL_THREADS), 0, s, a, total_tiles);
-    }
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipEventRecord(join, side);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
-    return e;
+    hipLaunchKernelGGL(k_seg_sort, dim3((unsigned)total_tiles), dim3(GSR_SEG_THREADS), 0, s, a);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -456,7 +594,7 @@ __device__ __forceinline__ uint32_t count_bucket(uint2 r)
 
 __global__ void k_order_zero(RangeArgs a)
 {
-    if (threadIdx.x < 66) a.buckets[threadIdx.x] = 0u;
+    if (threadIdx.x < 64) a.buckets[threadIdx.x] = 0u;
 }
 
 __global__ void k_order_count(RangeArgs a)
@@ -500,7 +638,7 @@ hipError_t launch_order(const RangeArgs& a, hipStream_t s)
 {
     if (a.total_tiles == 0) return hipSuccess;
     const int tb = (a.total_tiles + 255) / 256;
-    hipLaunchKernelGGL(k_order_zero, dim3(1), dim3(128), 0, s, a);
+    hipLaunchKernelGGL(k_order_zero, dim3(1), dim3(64), 0, s, a);
     hipLaunchKernelGGL(k_order_count, dim3(tb), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_order_place, dim3(tb), dim3(256), 0, s, a);
     return hipGetLastError();
