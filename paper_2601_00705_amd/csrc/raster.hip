@@ -23,8 +23,9 @@
 // reduces them on VALU cross-lane instructions (a transposed exchange of 8
 // values in 7 swaps plus 3 DPP adds, and one full sum), and 9 lanes add the
 // tile's totals to the slot's double accumulators with one atomic
-// instruction (plus one).  Per-pixel work is branch-free (selects); an entry
-// no lane of the wave needs is skipped as a whole.
+// instruction (plus one).  Within a pixel the work is branch-free (selects);
+// an entry no lane of the wave needs is skipped as a whole, and so are the
+// lane's pixels (rows of the tile) that an entry reaches in no lane.
 //
 // Both passes are bound by VALU issue where the tiles fill the chip (an entry
 // costs ~100 instructions of the forward's four pixels a lane, ~260 of the
@@ -35,8 +36,18 @@
 // scalar unit, and decided once per batch where it can be: with loops and
 // branches left divergent, predicates in vector registers and the clamp and
 // position tests on every entry, the backward took 2804 us on ten 1200x680
-// views of 1M Gaussians (now 2632) and 10325 us on 36 views of 3M (now 9346),
-// the forward 1310 us (now 1277).
+// views of 1M Gaussians (then 2632) and 10325 us on 36 views of 3M (then
+// 9346), the forward 1310 us (then 1277).
+//
+// An entry that reaches the tile reaches 85-90 % of its rows of pixels there
+// (those views hold large Gaussians), but 46 % where Gaussians are small (five
+// views of 500k: 27 of 256 pixels on average).  Skipping a row in which no
+// lane blends adds nothing to any sum, so the backward always does (one
+// scalar branch a row): 1123 -> 815 us on the five views, 2632 -> 2470 and
+// 9346 -> 8450 us on the others, 367 -> 300 us on 12 tiles of a 64x48 view.
+// The forward's row is half as long, and branches cost it more than they save
+// where most rows are reached (1277 -> 1365 us; 8 pixels a lane 4130 -> 4757):
+// it takes them in batches of mostly small entries (479 -> 419 us).
 #include "kernels.h"
 
 namespace gsr {
@@ -229,13 +240,25 @@ __device__ __forceinline__ bool may_clamp(float o, float amax)
     return (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(o)) >= __float_as_uint(amax);
 }
 
+// Whether the rows in which the entry can reach alpha_min lie within `half`
+// of its centre: with power2 = -log2(e)/2 d^T conic d, the rows at which it
+// is at least thr satisfy dy^2 <= -2 ln 2 thr A / (A C - B^2), and (a2, b2 / 2,
+// c2) are (A, B, C) scaled by -log2(e)/2.  A rule for speed only.
+__device__ __forceinline__ bool few_rows(const LdsRec& r, float half)
+{
+    const float det = r.p0.w * r.p1.y - 0.25f * r.p1.x * r.p1.x;
+    return r.p1.w * r.p0.w <= half * half * det;
+}
+
 // Walks the batch in LDS for the lane's pixels.  A pixel that has stopped
 // (or lies outside the view) carries a NaN row offset, so every later test
 // power2 >= thr fails for it without a per-pixel flag.  Reaching T_min is
 // rare (once per pixel at most), so the common step applies every passing
 // entry and a wave-uniform branch undoes the blend of stopping pixels.
 // CLAMPS: the batch holds an entry that may clamp, so every entry is asked.
-template <int PPT, bool COUNT, bool CLAMPS>
+// SMALL: most entries reach few of the lane's pixels' rows, and only the rows
+// that an entry reaches are composited (each a branch).
+template <int PPT, bool COUNT, bool CLAMPS, bool SMALL>
 __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t pos0, float amax, float tmin,
                                           float dx, float (&dy)[PPT], float (&T)[PPT], float (&C0)[PPT],
                                           float (&C1)[PPT], float (&C2)[PPT], uint32_t (&last)[PPT],
@@ -259,6 +282,33 @@ __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t p
             any |= pass[k];
         }
         if (any == 0) continue;
+        const uint32_t pos1 = pos0 + (uint32_t)e + 1u;
+        uint64_t stop[PPT], any_stop = 0;
+        if (SMALL) {
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                stop[k] = 0;
+                if (pass[k] == 0) continue;
+                const float a_raw = r.p1.z * __builtin_amdgcn_exp2f(p2[k]);
+                const float al = CLAMPS ? fminf(amax, a_raw) : a_raw;
+                const float Tn = __builtin_fmaf(-T[k], al, T[k]);
+                stop[k] = lanes(Tn < tmin) & pass[k];
+                any_stop |= stop[k];
+                const uint64_t blend = pass[k] & ~stop[k];
+                const float wgt = (in(blend) ? al : 0.0f) * T[k];
+                C0[k] = __builtin_fmaf(r.p2.x, wgt, C0[k]);
+                C1[k] = __builtin_fmaf(r.p2.y, wgt, C1[k]);
+                C2[k] = __builtin_fmaf(r.p2.z, wgt, C2[k]);
+                T[k] = in(blend) ? Tn : T[k];
+                last[k] = in(blend) ? pos1 : last[k];
+                if (COUNT) nb[k] += in(blend) ? 1u : 0u;
+            }
+            if (any_stop != 0) {
+#pragma unroll
+                for (int k = 0; k < PPT; ++k) dy[k] = in(stop[k]) ? __builtin_nanf("") : dy[k];
+            }
+            continue;
+        }
         float ab[PPT], Tn[PPT];
         if (CLAMPS && may_clamp(r.p1.z, amax)) {
 #pragma unroll
@@ -268,7 +318,6 @@ __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t p
 #pragma unroll
             for (int k = 0; k < PPT; ++k) ab[k] = in(pass[k]) ? r.p1.z * __builtin_amdgcn_exp2f(p2[k]) : 0.0f;
         }
-        uint64_t stop[PPT], any_stop = 0;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             Tn[k] = __builtin_fmaf(-T[k], ab[k], T[k]);
@@ -284,7 +333,6 @@ __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t p
                 pass[k] &= ~stop[k];
             }
         }
-        const uint32_t pos1 = pos0 + (uint32_t)e + 1u;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             const float wgt = ab[k] * T[k];
@@ -321,20 +369,32 @@ __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>
 #pragma unroll
         for (int k = 0; k < PPT; ++k) live |= __builtin_amdgcn_ballot_w64(dy[k] == dy[k]);
         if (live == 0) break;
-        bool may = false;
+        bool may = false, small = false;
 #pragma unroll
         for (int r = 0; r < GSR_BATCH / 64; ++r) {
             const uint32_t j = base + lane + 64 * r;
-            if (j < range.y)
+            if (j < range.y) {
                 may |= !(stage_record<MIXED>(a, a.vals[j], c.xc, c.yc, rec[lane + 64 * r]) < amax);
+                if (PPT == 4 && r == 0) small = few_rows(rec[lane], 0.375f * (float)a.cfg.tile_h);
+            }
         }
+        const uint64_t few = lanes(small);
         const bool clamps = lanes(may) != 0;
         __syncthreads();
         const int cnt = (int)min((uint32_t)GSR_BATCH, range.y - base);
-        // with 8 pixels per lane a second copy of the loop costs registers
-        // that the waves need more (96 and spills instead of 88)
-        if (PPT > 4 || clamps) fwd_batch<PPT, COUNT, true>(rec, cnt, base - range.x, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
-        else fwd_batch<PPT, COUNT, false>(rec, cnt, base - range.x, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+        const uint32_t pos0 = base - range.x;
+        // small entries: more than half of the batch's first 64 reach no more
+        // than three quarters of the tile's rows (half of them measured 428 us
+        // for 419 at the five views of 500k Gaussians); with fewer than four
+        // rows a lane there is little to skip.  With 8 pixels per lane a
+        // second copy of the loop costs registers that the waves need more
+        // (96 and spills instead of 88)
+        if (PPT == 4 && 2 * __popcll(few) > cnt / (GSR_BATCH / 64))
+            fwd_batch<PPT, COUNT, true, PPT == 4>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+        else if (PPT > 4 || clamps)
+            fwd_batch<PPT, COUNT, true, false>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+        else
+            fwd_batch<PPT, COUNT, false, false>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
         __syncthreads();
     }
 #pragma unroll
@@ -590,6 +650,7 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
     float c0s = 0.0f, c1s = 0.0f, c2s = 0.0f, D = 0.0f, Dy = 0.0f, Dyy = 0.0f;
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
+        if (on[k] == 0) continue;
         const float a_raw = r.p1.z * __builtin_amdgcn_exp2f(p2[k]);
         const float alpha = in(on[k]) ? (CLAMP ? fminf(a_raw, amax) : a_raw) : 0.0f;
         const float rcp = __builtin_amdgcn_rcpf(1.0f - alpha);
@@ -604,7 +665,7 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
         if (CLAMP) dd = a_raw < amax ? dd : 0.0f;
         gsk[k] = gsk_new;
         T[k] = Tb;
-        D = k == 0 ? dd : D + dd;
+        D += dd;
         Dy = __builtin_fmaf(dd, c.dy[k], Dy);
         Dyy = __builtin_fmaf(dd, dy2[k], Dyy);
     }
