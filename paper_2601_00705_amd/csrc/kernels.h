@@ -300,6 +300,9 @@ struct FrameArgs {
 #ifndef GSR_FWD_SPLIT
 #define GSR_FWD_SPLIT 2             // parts of a long tile (at most the pixels per lane)
 #endif
+#ifndef GSR_FWD_FEW_WAVES
+#define GSR_FWD_FEW_WAVES 8192      // most waves for which every tile is composited in parts
+#endif
 #define GSR_FWD_LONG_WAVES 2048     // persistent waves of the long tiles' parts (two per SIMD)
 
 hipError_t launch_project(const ProjectArgs& a, int sh_degree, hipStream_t s);

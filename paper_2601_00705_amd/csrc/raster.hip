@@ -346,9 +346,97 @@ __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t p
     }
 }
 
+// The same walk four entries at a time, for waves that run (nearly) alone on
+// their SIMD: the four alphas are independent, and only T passes from one to
+// the next.  T never grows, so no pixel stops within the four unless it ends
+// below T_min (or NaN); then they are taken one by one.  Records cnt .. up to
+// a multiple of four must be null (thr = +inf).
+template <int PPT, int GSR_BATCH, bool COUNT>
+__device__ __forceinline__ void fwd_batch4(const LdsRec* rec, int cnt, uint32_t pos0, float amax, float tmin,
+                                           float dx, float (&dy)[PPT], float (&T)[PPT], float (&C0)[PPT],
+                                           float (&C1)[PPT], float (&C2)[PPT], uint32_t (&last)[PPT],
+                                           uint32_t (&nb)[PPT])
+{
+    constexpr int U = 4;
+    for (int e = 0; e < cnt; e += U) {
+        if ((e & 15) == 0) {
+            uint64_t live = 0;
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) live |= __builtin_amdgcn_ballot_w64(dy[k] == dy[k]);
+            if (live == 0) break;
+        }
+        LdsRec r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = rec[e + u];
+        float ab[U][PPT];
+        uint64_t pass[U][PPT], any = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const ColTerms ct = col_terms(r[u], dx);
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                ab[u][k] = power2(ct, r[u].p1.y, dy[k]);
+                pass[u][k] = lanes(ab[u][k] >= r[u].p1.w);
+                any |= pass[u][k];
+            }
+        }
+        if (any == 0) continue;
+        float t[U + 1][PPT];
+        uint64_t stop = 0;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            t[0][k] = T[k];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float a_raw = r[u].p1.z * __builtin_amdgcn_exp2f(ab[u][k]);
+                ab[u][k] = in(pass[u][k]) ? fminf(amax, a_raw) : 0.0f;
+                t[u + 1][k] = __builtin_fmaf(-t[u][k], ab[u][k], t[u][k]);
+            }
+            stop |= lanes(!(t[U][k] >= tmin));
+        }
+        const uint32_t pos1 = pos0 + (uint32_t)e + 1u;
+        if (stop != 0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int k = 0; k < PPT; ++k) {
+                    // (a pixel that stops passes none of the later three)
+                    const uint64_t now = pass[u][k] & lanes(dy[k] == dy[k]);
+                    const float al = in(now) ? ab[u][k] : 0.0f;
+                    const float Tn = __builtin_fmaf(-T[k], al, T[k]);
+                    const uint64_t stops = lanes(Tn < tmin), blend = now & ~stops;
+                    const float wgt = (in(stops) ? 0.0f : al) * T[k];
+                    C0[k] = __builtin_fmaf(r[u].p2.x, wgt, C0[k]);
+                    C1[k] = __builtin_fmaf(r[u].p2.y, wgt, C1[k]);
+                    C2[k] = __builtin_fmaf(r[u].p2.z, wgt, C2[k]);
+                    T[k] = in(stops) ? T[k] : Tn;
+                    dy[k] = in(stops) ? __builtin_nanf("") : dy[k];
+                    last[k] = in(blend) ? pos1 + (uint32_t)u : last[k];
+                    if (COUNT) nb[k] += in(blend) ? 1u : 0u;
+                }
+            }
+            continue;
+        }
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float wgt = ab[u][k] * t[u][k];
+                C0[k] = __builtin_fmaf(r[u].p2.x, wgt, C0[k]);
+                C1[k] = __builtin_fmaf(r[u].p2.y, wgt, C1[k]);
+                C2[k] = __builtin_fmaf(r[u].p2.z, wgt, C2[k]);
+                last[k] = in(pass[u][k]) ? pos1 + (uint32_t)u : last[k];
+                if (COUNT) nb[k] += in(pass[u][k]) ? 1u : 0u;
+            }
+            T[k] = t[U][k];
+        }
+    }
+}
+
 // COUNT: also count the blended entries per pixel (into a.n_blend); a
-// separate instantiation, so that the plain forward carries no counters
-template <int PPT, int GSR_BATCH, bool COUNT, bool MIXED>
+// separate instantiation, so that the plain forward carries no counters.
+// ALONE: the waves are too few to hide each other's latencies (fwd_batch4).
+template <int PPT, int GSR_BATCH, bool COUNT, bool MIXED, bool ALONE>
 __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>& c, LdsRec* rec)
 {
     const int lane = threadIdx.x;
@@ -375,7 +463,11 @@ __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>
             const uint32_t j = base + lane + 64 * r;
             if (j < range.y) {
                 may |= !(stage_record<MIXED>(a, a.vals[j], c.xc, c.yc, rec[lane + 64 * r]) < amax);
-                if (PPT == 4 && r == 0) small = few_rows(rec[lane], 0.375f * (float)a.cfg.tile_h);
+                if (!ALONE && PPT == 4 && r == 0) small = few_rows(rec[lane], 0.375f * (float)a.cfg.tile_h);
+            } else if (ALONE) {
+                rec[lane + 64 * r].p0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                rec[lane + 64 * r].p1 = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
+                rec[lane + 64 * r].p2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
         }
         const uint64_t few = lanes(small);
@@ -389,7 +481,9 @@ __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>
         // rows a lane there is little to skip.  With 8 pixels per lane a
         // second copy of the loop costs registers that the waves need more
         // (96 and spills instead of 88)
-        if (PPT == 4 && 2 * __popcll(few) > cnt / (GSR_BATCH / 64))
+        if (ALONE) {
+            fwd_batch4<PPT, GSR_BATCH, COUNT>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+        } else if (PPT == 4 && 2 * __popcll(few) > cnt / (GSR_BATCH / 64))
             fwd_batch<PPT, COUNT, true, PPT == 4>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
         else if (PPT > 4 || clamps)
             fwd_batch<PPT, COUNT, true, false>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
@@ -478,7 +572,25 @@ __global__ __launch_bounds__(64, 5) void k_raster_fwd(RasterArgs a)
         const uint2 r = tile_range(a, c.tile);
         if (r.y - r.x >= long_threshold(a)) return;  // composited in parts by k_raster_fwd_long
     }
-    fwd_tile<PPT, GSR_BATCH, COUNT, MIXED>(a, c, rec);
+    fwd_tile<PPT, GSR_BATCH, COUNT, MIXED, false>(a, c, rec);
+}
+
+// Few tiles: every tile in PARTS parts, each a wave with PPT / PARTS of the
+// lane's pixels and the whole list.  A lone wave's entry takes 650 cycles,
+// two and a half times its issue (the chain of LDS read, alpha, T and the
+// branches): 12 tiles of 716 entries 196 us, 1200 tiles of 162 (up to 332)
+// entries 92 us, 825 of 104 77 us.  In four parts of one pixel a lane, four
+// entries at a time, these take 65, 46 and 31 us; 3225 tiles of 318 entries,
+// in two parts, 197 -> 154 us (in four 182: the parts' record reads fill the
+// LDS; two entries at a time 162; records read ahead into registers 174).
+template <int PPT, int PARTS, int GSR_BATCH, bool COUNT, bool MIXED>
+__global__ __launch_bounds__(64, PPT / PARTS <= 2 ? 6 : 4) void k_raster_fwd_few(RasterArgs a)
+{
+    constexpr int Q = PPT / PARTS;
+    __shared__ LdsRec rec[GSR_BATCH];
+    const int tile = uniform((int)a.order[blockIdx.x / PARTS]);
+    const TileCtx<Q> c = tile_ctx_at<Q>(a, tile, (int)(blockIdx.x % PARTS) * Q);
+    fwd_tile<Q, GSR_BATCH, COUNT, MIXED, true>(a, c, rec);
 }
 
 // Persistent waves that take (long tile, part) items from a queue (zeroed
@@ -506,12 +618,12 @@ __global__ __launch_bounds__(64, 5) void k_raster_fwd_long(RasterArgs a, int tot
         if ((int)item < items2) {
             const int tile = (int)a.order[item / S2];
             const TileCtx<Q2> c = tile_ctx_at<Q2>(a, tile, (int)(item % S2) * Q2);
-            fwd_tile<Q2, GSR_BATCH, COUNT, MIXED>(a, c, rec);
+            fwd_tile<Q2, GSR_BATCH, COUNT, MIXED, false>(a, c, rec);
         } else {
             const uint32_t j = item - (uint32_t)items2;
             const int tile = (int)a.order[k2 + (int)(j / S)];
             const TileCtx<Q> c = tile_ctx_at<Q>(a, tile, (int)(j % S) * Q);
-            fwd_tile<Q, GSR_BATCH, COUNT, MIXED>(a, c, rec);
+            fwd_tile<Q, GSR_BATCH, COUNT, MIXED, false>(a, c, rec);
         }
     }
 }
@@ -823,37 +935,81 @@ __global__ __launch_bounds__(64, PPT <= 4 ? 5 : 3) void k_raster_bwd(RasterArgs 
     view_done(a, c.tile, lane);
 }
 
-template <int PPT, int B, bool COUNT, bool MIXED>
-static void launch_fwd_b(const RasterArgs& a, int tiles, hipStream_t s, hipStream_t side)
+// Parts of every tile: as many (up to the lane's pixels) as keep the waves at
+// GSR_FWD_FEW_WAVES (8 to a SIMD, what is resident at once) or less; with
+// more tiles the chip is full and the parts' repeated work per entry costs
+// what they gain (16125 tiles: 419 us whole).  The parts stage 64 records at
+// a time whatever the plan's batch, which changes no result: 4 KB of LDS
+// leave room for the 8 waves.
+static int fwd_parts(int tiles, int ppt)
 {
+    int parts = ppt;
+    while (parts > 1 && (int64_t)tiles * parts > GSR_FWD_FEW_WAVES) parts /= 2;
+    return parts;
+}
+
+template <int PPT, int PARTS, int B, bool COUNT, bool MIXED>
+static void launch_fwd_few(const RasterArgs& a, int tiles, int parts, hipStream_t s)
+{
+    if constexpr (PARTS > 1) {
+        if (parts == PARTS)
+            hipLaunchKernelGGL((k_raster_fwd_few<PPT, PARTS, B, COUNT, MIXED>), dim3((unsigned)tiles * PARTS), dim3(64),
+                               0, s, a);
+        else
+            launch_fwd_few<PPT, PARTS / 2, B, COUNT, MIXED>(a, tiles, parts, s);
+    }
+}
+
+template <int PPT, int B, bool COUNT, bool MIXED>
+static hipError_t launch_fwd_b(const RasterArgs& a, int tiles, hipStream_t s, hipStream_t side, hipEvent_t fork,
+                               hipEvent_t join)
+{
+    const int parts = fwd_parts(tiles, PPT);
+    if (parts > 1) {
+        launch_fwd_few<PPT, PPT, 64, COUNT, MIXED>(a, tiles, parts, s);
+        return hipGetLastError();
+    }
+    // the long tiles' parts run on `side`, forked from `s` and joined back
+    // (the fork and join are graph edges when `s` is being captured)
+    hipError_t e = hipSuccess;
     if (FwdSplit<PPT>::parts > 1) {
+        e = hipEventRecord(fork, s);
+        if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_zero_queue, dim3(1), dim3(1), 0, side, a.fwd_queue);
         hipLaunchKernelGGL((k_raster_fwd_long<PPT, B, COUNT, MIXED>), dim3(GSR_FWD_LONG_WAVES), dim3(64), 0, side,
                            a, tiles);
     }
     hipLaunchKernelGGL((k_raster_fwd<PPT, B, COUNT, MIXED>), dim3(tiles), dim3(64), 0, s, a);
+    e = hipGetLastError();
+    if (FwdSplit<PPT>::parts > 1) {
+        if (e == hipSuccess) e = hipEventRecord(join, side);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
+    }
+    return e;
 }
 
 template <int PPT, bool COUNT, bool MIXED>
-static hipError_t launch_fwd_c(const RasterArgs& a, int tiles, int batch, hipStream_t s, hipStream_t side)
+static hipError_t launch_fwd_c(const RasterArgs& a, int tiles, int batch, hipStream_t s, hipStream_t side,
+                               hipEvent_t fork, hipEvent_t join)
 {
     switch (batch) {
-    case 64: launch_fwd_b<PPT, 64, COUNT, MIXED>(a, tiles, s, side); break;
-    case 128: launch_fwd_b<PPT, 128, COUNT, MIXED>(a, tiles, s, side); break;
-    case 256: launch_fwd_b<PPT, 256, COUNT, MIXED>(a, tiles, s, side); break;
+    case 64: return launch_fwd_b<PPT, 64, COUNT, MIXED>(a, tiles, s, side, fork, join);
+    case 128: return launch_fwd_b<PPT, 128, COUNT, MIXED>(a, tiles, s, side, fork, join);
+    case 256: return launch_fwd_b<PPT, 256, COUNT, MIXED>(a, tiles, s, side, fork, join);
     default: return hipErrorInvalidValue;
     }
-    return hipSuccess;
 }
 
 template <int PPT>
-static hipError_t launch_fwd_t(const RasterArgs& a, int tiles, int batch, hipStream_t s, hipStream_t side)
+static hipError_t launch_fwd_t(const RasterArgs& a, int tiles, int batch, hipStream_t s, hipStream_t side,
+                               hipEvent_t fork, hipEvent_t join)
 {
     if (a.cfg.mixed)
-        return a.n_blend ? launch_fwd_c<PPT, true, true>(a, tiles, batch, s, side)
-                         : launch_fwd_c<PPT, false, true>(a, tiles, batch, s, side);
-    return a.n_blend ? launch_fwd_c<PPT, true, false>(a, tiles, batch, s, side)
-                     : launch_fwd_c<PPT, false, false>(a, tiles, batch, s, side);
+        return a.n_blend ? launch_fwd_c<PPT, true, true>(a, tiles, batch, s, side, fork, join)
+                         : launch_fwd_c<PPT, false, true>(a, tiles, batch, s, side, fork, join);
+    return a.n_blend ? launch_fwd_c<PPT, true, false>(a, tiles, batch, s, side, fork, join)
+                     : launch_fwd_c<PPT, false, false>(a, tiles, batch, s, side, fork, join);
 }
 
 template <int PPT, bool DET, bool MIXED>
@@ -878,26 +1034,17 @@ static hipError_t launch_bwd_t(const RasterArgs& a, int tiles, int batch, hipStr
                  : launch_bwd_d<PPT, false, false>(a, tiles, batch, s);
 }
 
-// The long tiles' parts run on `side`, forked from `s` and joined back (the
-// fork and join are graph edges when `s` is being captured).
 hipError_t launch_raster_fwd(const RasterArgs& a, int total_tiles, int tile_px, int batch, hipStream_t s,
                              hipStream_t side, hipEvent_t fork, hipEvent_t join)
 {
     if (total_tiles == 0) return hipSuccess;
-    hipError_t e = hipEventRecord(fork, s);
-    if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
-    if (e != hipSuccess) return e;
     switch (tile_px) {
-    case 64: e = launch_fwd_t<1>(a, total_tiles, batch, s, side); break;
-    case 128: e = launch_fwd_t<2>(a, total_tiles, batch, s, side); break;
-    case 256: e = launch_fwd_t<4>(a, total_tiles, batch, s, side); break;
-    case 512: e = launch_fwd_t<8>(a, total_tiles, batch, s, side); break;
+    case 64: return launch_fwd_t<1>(a, total_tiles, batch, s, side, fork, join);
+    case 128: return launch_fwd_t<2>(a, total_tiles, batch, s, side, fork, join);
+    case 256: return launch_fwd_t<4>(a, total_tiles, batch, s, side, fork, join);
+    case 512: return launch_fwd_t<8>(a, total_tiles, batch, s, side, fork, join);
     default: return hipErrorInvalidValue;
     }
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e == hipSuccess) e = hipEventRecord(join, side);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
-    return e;
 }
 
 // zero the screen-space accumulators of every projected slot (rx >= 0) when
