@@ -303,6 +303,10 @@ struct FrameArgs {
 #ifndef GSR_FWD_FEW_WAVES
 #define GSR_FWD_FEW_WAVES 8192      // most waves for which every tile is composited in parts
 #endif
+#ifndef GSR_BWD_FEW_TILES
+#define GSR_BWD_FEW_TILES 1536      // most tiles whose backward deals a tile to several waves
+#endif
+#define GSR_BWD_GROUP 8             // entries between its barriers
 #define GSR_FWD_LONG_WAVES 2048     // persistent waves of the long tiles' parts (two per SIMD)
 
 hipError_t launch_project(const ProjectArgs& a, int sh_degree, hipStream_t s);

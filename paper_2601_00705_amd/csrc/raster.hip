@@ -197,7 +197,7 @@ __device__ __forceinline__ TileCtx<PPT> tile_ctx_at(const RasterArgs& a, int til
     const int lt = tile - vw.tile_base;
     const int ty = lt / vw.tiles_x;
     const int tx = lt - ty * vw.tiles_x;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int l2 = a.cfg.log2_tw;
     c.px = tx * a.cfg.tile_w + (lane & (a.cfg.tile_w - 1));
     c.rs = 64 >> l2;
@@ -740,9 +740,87 @@ struct PendingField {
     float w;
 };
 
+// The sums of an entry's terms over a lane's pixels.
+struct PixelSums {
+    float D = 0.0f, Dy = 0.0f, Dyy = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    // a pixel's dd = alpha dL/dalpha and weight, its upstream gradient and
+    // its row offset (and that squared)
+    __device__ __forceinline__ void add(float dd, float wgt, float g0, float g1, float g2, float dy, float dyy)
+    {
+        c0 = __builtin_fmaf(g0, wgt, c0);
+        c1 = __builtin_fmaf(g1, wgt, c1);
+        c2 = __builtin_fmaf(g2, wgt, c2);
+        D += dd;
+        Dy = __builtin_fmaf(dd, dy, Dy);
+        Dyy = __builtin_fmaf(dd, dyy, Dyy);
+    }
+};
+
+// The lane's nine screen-space partials of an entry.  power2 partials per
+// pixel: d/du = -(2 a2 dx + b2 dy + gx), d/dv = -(b2 dx + 2 c2 dy + gy) (d =
+// pixel - tile centre), and d/d(A, B, C) = k (fx^2, 2 fx fy, fy^2) with (fx,
+// fy) = d + o the offset from the projected centre; d alpha / d o = alpha / o.
+__device__ __forceinline__ void bwd_partials(const LdsRec& r, const ColTerms& ct, float dx, const PixelSums& p,
+                                             float (&v)[9])
+{
+    const float fx = dx + r.p3.x;
+    const float Fy = __builtin_fmaf(r.p3.y, p.D, p.Dy);  // sum dd fy
+    // (2 a2 dx as a2 (2 dx): the same product, with 2 dx a constant of the lane)
+    v[0] = __builtin_fmaf(__builtin_fmaf(r.p0.w, 2.0f * dx, r.p0.y), p.D, r.p1.x * p.Dy);
+    v[1] = __builtin_fmaf(ct.s1, p.D, r.p3.w * p.Dy);
+    v[2] = fx * (fx * p.D);
+    v[3] = fx * Fy;
+    v[4] = __builtin_fmaf(r.p3.y, Fy + p.Dy, p.Dyy);
+    v[5] = p.D;
+    v[6] = p.c0;
+    v[7] = p.c1;
+    v[8] = p.c2;
+}
+
+// Adds an entry's first eight reduced fields (lane 8 f holds field f's).
+template <bool DET>
+__device__ __forceinline__ void bwd_add8(const RasterArgs& a, uint32_t slot, float s, float inv_o, int lane)
+{
+    if ((lane & 7) != 0) return;
+    const int f = lane >> 3;
+    const float value = s * (f == 5 ? inv_o : field_scale(f));
+    if (DET) {
+        add_field<DET>(a, slot, f, value);
+    } else {
+        // the slot's address stays scalar (left to itself the compiler folds
+        // it into a 64-bit multiply-add per lane)
+        uint64_t base = (uint64_t)a.grad2d + sizeof(double) * GSR_G2 * (uint64_t)slot;
+        asm("" : "+s"(base));
+        typedef __attribute__((address_space(1))) double global_double;
+        __builtin_amdgcn_global_atomic_fadd_f64(reinterpret_cast<global_double*>(base) + (uint32_t)f, (double)value);
+    }
+}
+
+// The wave's reduction of an entry's partials and their addition to the
+// slot's accumulators.
+template <bool DET>
+__device__ __forceinline__ void bwd_reduce(const RasterArgs& a, const LdsRec& r, const ColTerms& ct, float dx,
+                                           const PixelSums& p, int lane, PendingField& pend)
+{
+    float v[9];
+    bwd_partials(r, ct, dx, p, v);
+    const float s = wave_sum8_transposed(v, lane);
+    const uint32_t slot = (uint32_t)uniform(__float_as_int(r.p2.w));
+    bwd_add8<DET>(a, slot, s, r.p3.z, lane);
+    if (uniform(pend.have)) {
+        // lane 1 holds the waiting entry's total, lane 33 this one's
+        const float w = wave_sum_pair(pend.w, v[8]);
+        if ((lane & 31) == 1) add_field<DET>(a, lane < 32 ? (uint32_t)pend.slot : slot, 8, w);
+        pend.have = 0;
+    } else {
+        pend.w = v[8];
+        pend.slot = (int)slot;
+        pend.have = 1;
+    }
+}
+
 // One entry of the backward replay for the lane's pixels, then the wave's
-// reduction of the entry's nine screen-space partials and their addition to
-// the slot's accumulators.  Per pixel, with rcp = 1 / (1 - alpha), T_j = T
+// reduction (bwd_reduce).  Per pixel, with rcp = 1 / (1 - alpha), T_j = T
 // rcp the transmittance before the entry, gcol = g . c and gsk the running
 // g . (colour behind) + dL/dT_final T_final:
 //   dL/dalpha = T_j gcol - gsk rcp,
@@ -759,7 +837,7 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
                                           const float (&g2)[PPT], const float (&dy2)[PPT], float (&T)[PPT],
                                           float (&gsk)[PPT], int lane, PendingField& pend)
 {
-    float c0s = 0.0f, c1s = 0.0f, c2s = 0.0f, D = 0.0f, Dy = 0.0f, Dyy = 0.0f;
+    PixelSums p;
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         if (on[k] == 0) continue;
@@ -769,61 +847,14 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
         const float Tb = T[k] * rcp;
         const float gcol = __builtin_fmaf(g0[k], r.p2.x, __builtin_fmaf(g1[k], r.p2.y, g2[k] * r.p2.z));
         const float wgt = alpha * Tb;
-        c0s = __builtin_fmaf(g0[k], wgt, c0s);
-        c1s = __builtin_fmaf(g1[k], wgt, c1s);
-        c2s = __builtin_fmaf(g2[k], wgt, c2s);
         const float gsk_new = __builtin_fmaf(wgt, gcol, gsk[k]);
         float dd = __builtin_fmaf(-gsk[k], rcp, gsk_new);
         if (CLAMP) dd = a_raw < amax ? dd : 0.0f;
         gsk[k] = gsk_new;
         T[k] = Tb;
-        D += dd;
-        Dy = __builtin_fmaf(dd, c.dy[k], Dy);
-        Dyy = __builtin_fmaf(dd, dy2[k], Dyy);
+        p.add(dd, wgt, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
     }
-    // power2 partials per pixel: d/du = -(2 a2 dx + b2 dy + gx),
-    // d/dv = -(b2 dx + 2 c2 dy + gy) (d = pixel - tile centre), and
-    // d/d(A, B, C) = k (fx^2, 2 fx fy, fy^2) with (fx, fy) = d + o the
-    // offset from the projected centre; d alpha / d o = alpha / o
-    const float fx = c.dx + r.p3.x;
-    const float Fy = __builtin_fmaf(r.p3.y, D, Dy);  // sum dd fy
-    float v[9];
-    // (2 a2 dx as a2 (2 dx): the same product, with 2 dx a constant of the lane)
-    v[0] = __builtin_fmaf(__builtin_fmaf(r.p0.w, 2.0f * c.dx, r.p0.y), D, r.p1.x * Dy);
-    v[1] = __builtin_fmaf(ct.s1, D, r.p3.w * Dy);
-    v[2] = fx * (fx * D);
-    v[3] = fx * Fy;
-    v[4] = __builtin_fmaf(r.p3.y, Fy + Dy, Dyy);
-    v[5] = D;
-    v[6] = c0s;
-    v[7] = c1s;
-    v[8] = c2s;
-    const float s = wave_sum8_transposed(v, lane);
-    const uint32_t slot = (uint32_t)uniform(__float_as_int(r.p2.w));
-    if ((lane & 7) == 0) {
-        const int f = lane >> 3;
-        const float value = s * (f == 5 ? r.p3.z : field_scale(f));
-        if (DET) {
-            add_field<DET>(a, slot, f, value);
-        } else {
-            // the slot's address stays scalar (left to itself the compiler
-            // folds it into a 64-bit multiply-add per lane)
-            uint64_t base = (uint64_t)a.grad2d + sizeof(double) * GSR_G2 * (uint64_t)slot;
-            asm("" : "+s"(base));
-            typedef __attribute__((address_space(1))) double global_double;
-            __builtin_amdgcn_global_atomic_fadd_f64(reinterpret_cast<global_double*>(base) + (uint32_t)f, (double)value);
-        }
-    }
-    if (uniform(pend.have)) {
-        // lane 1 holds the waiting entry's total, lane 33 this one's
-        const float w = wave_sum_pair(pend.w, v[8]);
-        if ((lane & 31) == 1) add_field<DET>(a, lane < 32 ? (uint32_t)pend.slot : slot, 8, w);
-        pend.have = 0;
-    } else {
-        pend.w = v[8];
-        pend.slot = (int)slot;
-        pend.have = 1;
-    }
+    bwd_reduce<DET>(a, r, ct, c.dx, p, lane, pend);
 }
 
 // The staged entries rec[0, cnt), from the list's position top down.
@@ -935,6 +966,219 @@ __global__ __launch_bounds__(64, PPT <= 4 ? 5 : 3) void k_raster_bwd(RasterArgs 
     view_done(a, c.tile, lane);
 }
 
+// Few tiles: 2 W waves to a tile.  Entries are replayed GSR_BWD_GROUP at a
+// time.  The lane's pixels are dealt to the first W waves, which run a group
+// through them (four entries' alphas in flight, only T and gsk passing from
+// one to the next) and leave each pixel's two terms, alpha dL/dalpha and the
+// weight, in LDS; meanwhile the other W waves take whole entries of the group
+// before, add all of the lane's pixels up in the single wave's order and
+// reduce them, two entries at a time.  The arithmetic and its order are those
+// of k_raster_bwd, the sums equal bit for bit.  Terms and staged records are
+// double-buffered, so a group costs one barrier, and a batch is staged while
+// the one before is replayed.  A lone wave's entry takes 1000 cycles, twice
+// its issue; here a group of 8 takes as long as its replay or its reduction,
+// about 2700.  12 tiles of 716 entries 297 -> 101 us (the same waves doing
+// both in turn 156), 1200 tiles of 162 137 -> 100, 825 of 104 in deterministic
+// mode 150 -> 76, 1200 tiles of 512 pixels 743 -> 550 us; but 2400 tiles of 256
+// pixels 684 -> 796 us: the passes through LDS are issue that a full chip
+// lacks, hence GSR_BWD_FEW_TILES (1.5 tiles to a SIMD).
+template <int PPT>
+struct BwdFew {
+    static constexpr int waves = PPT < 4 ? PPT : 4;  // W
+    static constexpr int ppt = PPT / waves;          // pixels a lane of one wave
+};
+
+template <int PPT, bool DET, bool MIXED>
+__global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(RasterArgs a)
+{
+    constexpr int W = BwdFew<PPT>::waves, Q = BwdFew<PPT>::ppt, G = GSR_BWD_GROUP, U = 4, B = 64;
+    static_assert(G % U == 0 && B % G == 0 && B / G >= 4 && W <= 4 && G % (2 * W) == 0, "");
+    __shared__ LdsRec rec[2][B];
+    __shared__ float2 term[2][G][PPT][64];
+    __shared__ uint32_t reached[2][4];  // entries that reach wave w's pixels, a bit each
+    const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
+    const bool replays = wave < W;
+    const int w = replays ? wave : wave - W;
+    const int tile = uniform((int)a.order[blockIdx.x]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.counters->grad_dirty = 1u;
+    if (uniform((int)a.counters->overflow)) {
+        view_done(a, tile, (int)threadIdx.x);
+        return;
+    }
+    const TileCtx<PPT> c = tile_ctx_at<PPT>(a, tile, 0);
+    const uint2 range = tile_range(a, tile);
+    uint32_t lane_max = 0;
+#pragma unroll
+    for (int k = 0; k < PPT; ++k)
+        if (c.inside(k)) lane_max = max(lane_max, (uint32_t)a.n_contrib_in[c.pix(k)]);
+    for (int off = 32; off > 0; off >>= 1) lane_max = max(lane_max, (uint32_t)__shfl_xor((int)lane_max, off, 64));
+    // entries to replay, from position count - 1 down
+    const int count = (int)min((uint32_t)uniform((int)lane_max), range.y - range.x);
+    const int groups = (count + G - 1) / G;
+    // records i .. i + B - 1 of the replay, null past its end
+    auto stage = [&](int i) {
+        LdsRec& r = rec[(i / B) & 1][lane];
+        if (i + lane < count) {
+            stage_record<MIXED>(a, a.vals[range.x + (uint32_t)(count - 1 - i - lane)], c.xc, c.yc, r);
+        } else {
+            r.p0 = r.p2 = r.p3 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            r.p1 = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
+        }
+    };
+    if (wave == W) stage(0);
+
+    if (replays) {
+        const float amax = a.cfg.alpha_max;
+        const TileCtx<Q> o = tile_ctx_at<Q>(a, tile, w * Q);
+        float T[Q], gsk[Q], h0[Q], h1[Q], h2[Q];
+        uint32_t my_n[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            float Tf = 1.0f, gT = 0.0f;
+            h0[q] = h1[q] = h2[q] = 0.0f;
+            my_n[q] = 0u;
+            if (o.inside(q)) {
+                Tf = a.T_final_in[o.pix(q)];
+                my_n[q] = (uint32_t)a.n_contrib_in[o.pix(q)];
+                h0[q] = a.dL_drgb[o.rgb0(q)];
+                h1[q] = a.dL_drgb[o.rgb0(q) + o.plane];
+                h2[q] = a.dL_drgb[o.rgb0(q) + 2 * o.plane];
+                if (a.dL_dT) gT = a.dL_dT[o.pix(q)];
+            }
+            T[q] = Tf;
+            gsk[q] = __builtin_fmaf(gT, Tf, Tf * (h0[q] * a.cfg.bg0 + h1[q] * a.cfg.bg1 + h2[q] * a.cfg.bg2));
+        }
+        __syncthreads();
+        for (int gr = 0; gr < groups; ++gr) {
+            const LdsRec* rg = &rec[(gr * G / B) & 1][gr * G % B];
+            const int buf = gr & 1;
+            const uint32_t top = (uint32_t)(count - 1 - gr * G);  // (below 0 only at null records)
+            uint32_t reach = 0;
+#pragma unroll
+            for (int e = 0; e < G; e += U) {
+                LdsRec r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) r[u] = rg[e + u];
+                float p2[U][Q], alpha[U][Q], rcp[U][Q], gcol[U][Q];
+                uint64_t on[U][Q], any = 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const ColTerms ct = col_terms(r[u], o.dx);
+                    uint64_t any_u = 0;
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        p2[u][q] = power2(ct, r[u].p1.y, o.dy[q]);
+                        on[u][q] = lanes(p2[u][q] >= r[u].p1.w) & lanes(top - (uint32_t)(e + u) < my_n[q]);
+                        any_u |= on[u][q];
+                    }
+                    reach |= any_u != 0 ? 1u << (e + u) : 0u;
+                    any |= any_u;
+                }
+                if (any == 0) continue;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const float lim = may_clamp(r[u].p1.z, amax) ? amax : INFINITY;
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        p2[u][q] = r[u].p1.z * __builtin_amdgcn_exp2f(p2[u][q]);
+                        alpha[u][q] = in(on[u][q]) ? fminf(p2[u][q], lim) : 0.0f;
+                        rcp[u][q] = __builtin_amdgcn_rcpf(1.0f - alpha[u][q]);
+                        gcol[u][q] = __builtin_fmaf(h0[q], r[u].p2.x, __builtin_fmaf(h1[q], r[u].p2.y, h2[q] * r[u].p2.z));
+                        on[u][q] = lanes(p2[u][q] < lim);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        const float Tb = T[q] * rcp[u][q];
+                        const float wgt = alpha[u][q] * Tb;
+                        const float gsk_new = __builtin_fmaf(wgt, gcol[u][q], gsk[q]);
+                        const float dd = __builtin_fmaf(-gsk[q], rcp[u][q], gsk_new);
+                        gsk[q] = gsk_new;
+                        T[q] = Tb;
+                        term[buf][e + u][w * Q + q][lane] = make_float2(in(on[u][q]) ? dd : 0.0f, wgt);
+                    }
+                }
+            }
+            if (lane == 0) reached[buf][w] = reach;
+            __syncthreads();
+        }
+    } else {
+        float g0[PPT], g1[PPT], g2[PPT], dy2[PPT];
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            g0[k] = g1[k] = g2[k] = 0.0f;
+            if (c.inside(k)) {
+                g0[k] = a.dL_drgb[c.rgb0(k)];
+                g1[k] = a.dL_drgb[c.rgb0(k) + c.plane];
+                g2[k] = a.dL_drgb[c.rgb0(k) + 2 * c.plane];
+            }
+            dy2[k] = c.dy[k] * c.dy[k];
+        }
+        PendingField pend{0, 0, 0.0f};
+        __syncthreads();
+        // step gr reduces group gr - 1 (after the last barrier, the last)
+        for (int gr = 0; gr <= groups; ++gr) {
+            // the batch after this one, once the one before it is reduced
+            if (w == 0 && gr % (B / G) == 2 && (gr / (B / G) + 1) * B < count) stage((gr / (B / G) + 1) * B);
+            if (gr > 0) {
+                const LdsRec* rg = &rec[((gr - 1) * G / B) & 1][(gr - 1) * G % B];
+                const int buf = (gr - 1) & 1;
+                uint32_t hit[W], hits = 0;
+#pragma unroll
+                for (int k = 0; k < W; ++k) {
+                    hit[k] = (uint32_t)uniform((int)reached[buf][k]);
+                    hits |= hit[k];
+                }
+                // this wave's entries, two at a time (their reductions overlap)
+#pragma unroll
+                for (int e = 0; e < G; e += 2 * W) {
+                    const int e0 = e + w, e1 = e + w + W;
+                    const bool has0 = (hits >> e0) & 1u, has1 = (hits >> e1) & 1u;
+                    if (!has0 && !has1) continue;
+                    const LdsRec r0 = rg[e0], r1 = rg[e1];
+                    float2 t0[PPT], t1[PPT];
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) {
+                        t0[k] = term[buf][e0][k][lane];
+                        t1[k] = term[buf][e1][k][lane];
+                    }
+                    PixelSums p0, p1;
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) {
+                        if ((hit[k / Q] >> e0) & 1u) p0.add(t0[k].x, t0[k].y, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+                        if ((hit[k / Q] >> e1) & 1u) p1.add(t1[k].x, t1[k].y, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+                    }
+                    if (has0 && has1) {
+                        float v0[9], v1[9];
+                        bwd_partials(r0, col_terms(r0, c.dx), c.dx, p0, v0);
+                        bwd_partials(r1, col_terms(r1, c.dx), c.dx, p1, v1);
+                        const float s0 = wave_sum8_transposed(v0, lane), s1 = wave_sum8_transposed(v1, lane);
+                        const float x = wave_sum_pair(v0[8], v1[8]);
+                        const uint32_t slot0 = (uint32_t)uniform(__float_as_int(r0.p2.w));
+                        const uint32_t slot1 = (uint32_t)uniform(__float_as_int(r1.p2.w));
+                        bwd_add8<DET>(a, slot0, s0, r0.p3.z, lane);
+                        bwd_add8<DET>(a, slot1, s1, r1.p3.z, lane);
+                        if ((lane & 31) == 1) add_field<DET>(a, lane < 32 ? slot0 : slot1, 8, x);
+                    } else if (has0) {
+                        bwd_reduce<DET>(a, r0, col_terms(r0, c.dx), c.dx, p0, lane, pend);
+                    } else {
+                        bwd_reduce<DET>(a, r1, col_terms(r1, c.dx), c.dx, p1, lane, pend);
+                    }
+                }
+            }
+            if (gr < groups) __syncthreads();
+        }
+        if (uniform(pend.have)) {  // the last reduced entry's ninth field, alone
+            const float x = wave_sum_pair(pend.w, 0.0f);
+            if (lane == 1) add_field<DET>(a, (uint32_t)pend.slot, 8, x);
+        }
+    }
+    __syncthreads();
+    view_done(a, tile, (int)threadIdx.x);
+}
+
 // Parts of every tile: as many (up to the lane's pixels) as keep the waves at
 // GSR_FWD_FEW_WAVES (8 to a SIMD, what is resident at once) or less; with
 // more tiles the chip is full and the parts' repeated work per entry costs
@@ -1015,6 +1259,12 @@ static hipError_t launch_fwd_t(const RasterArgs& a, int tiles, int batch, hipStr
 template <int PPT, bool DET, bool MIXED>
 static hipError_t launch_bwd_d(const RasterArgs& a, int tiles, int batch, hipStream_t s)
 {
+    if constexpr (PPT > 1) {
+        if (tiles <= GSR_BWD_FEW_TILES) {  // (64 records at a time whatever the batch, which changes no result)
+            hipLaunchKernelGGL((k_raster_bwd_few<PPT, DET, MIXED>), dim3(tiles), dim3(128 * BwdFew<PPT>::waves), 0, s, a);
+            return hipSuccess;
+        }
+    }
     switch (batch) {
     case 64: hipLaunchKernelGGL((k_raster_bwd<PPT, 64, DET, MIXED>), dim3(tiles), dim3(64), 0, s, a); break;
     case 128: hipLaunchKernelGGL((k_raster_bwd<PPT, 128, DET, MIXED>), dim3(tiles), dim3(64), 0, s, a); break;
