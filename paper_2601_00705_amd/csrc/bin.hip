@@ -22,8 +22,8 @@
 //                 with more than GSR_BIN_LDS_TILES tiles add straight into
 //                 the row)
 //   k_bin_colscan per tile: exclusive prefix of its column (the chunk's offset
-//                 inside the tile's segment) and the tile's total, four
-//                 waves to a column
+//                 inside the tile's segment) and the tile's total, 32
+//                 groups of threads to a column
 //   k_bin_tiles   the tile ranges from the column scan's per-block prefixes
 //                 and block sums, the pair count and the capacity flag
 //   k_bin_emit    the chunk's pairs, each at its tile's cursor (LDS atomics:
@@ -92,13 +92,29 @@ __device__ __forceinline__ uint32_t live_len(const BinArgs& a, int v)
     return c < (uint64_t)a.n ? c : (uint32_t)a.n;
 }
 
-__device__ __forceinline__ int view_chunks(const BinArgs& a, int v)
+// Entries of one chunk of a view with len live Gaussians: chunk_mult *
+// GSR_BIN_CHUNK, or fewer (a multiple of GSR_BIN_LEAST) where that would
+// leave the views' chunks below GSR_BIN_BLOCKS, so that a sparse view's work
+// still spreads over the chip: 8754 live of 100k Gaussians, 22 candidate
+// tiles each, made 35 chunks of 256, counted in 24 us and emitted in 27;
+// 137 of 64 take 16 and 17 (of 32: 13 and 14, and 2 more for their column
+// scan).  The count matrix has a.chunks rows a view.
+__device__ __forceinline__ uint32_t chunk_len(const BinArgs& a, uint32_t len)
 {
-    const uint32_t per = (uint32_t)a.chunk_mult * GSR_BIN_CHUNK;
-    return (int)((live_len(a, v) + per - 1u) / per);
+    const uint32_t full = (uint32_t)a.chunk_mult * GSR_BIN_CHUNK;
+    const uint32_t want = max(1u, (uint32_t)(GSR_BIN_BLOCKS / a.n_views));
+    if (len / want >= full) return full;
+    const uint32_t per = max((len + want - 1u) / want, (len + (uint32_t)a.chunks - 1u) / (uint32_t)a.chunks);
+    return min(full, (max(per, 1u) + GSR_BIN_LEAST - 1u) / GSR_BIN_LEAST * GSR_BIN_LEAST);
 }
 
-// entries base .. of view v's live list (len entries)
+__device__ __forceinline__ int view_chunks(const BinArgs& a, int v)
+{
+    const uint32_t len = live_len(a, v), per = chunk_len(a, len);
+    return (int)((len + per - 1u) / per);
+}
+
+// entries base .. (below len, the chunk's end) of view v's live list
 __device__ __forceinline__ void fetch_group(const BinArgs& a, int v, int64_t base, uint32_t len, bool want_depth,
                                             GroupRegs& R)
 {
@@ -334,14 +350,15 @@ __global__ __launch_bounds__(256) void k_bin_count(BinArgs a)
     __shared__ ChunkLds L;
     const int v = blockIdx.y;
     if ((int)blockIdx.x >= view_chunks(a, v)) return;
-    const uint32_t len = live_len(a, v);
+    const uint32_t live = live_len(a, v), per_chunk = chunk_len(a, live);
+    const uint32_t len = min(live, ((uint32_t)blockIdx.x + 1u) * per_chunk);  // the chunk's end
     const ViewInfo vw = a.views->v[v];
     const int tiles_v = vw.tiles_x * vw.tiles_y;
     uint32_t* row = count_row(a, vw, blockIdx.x);
     if (LDS_HIST)
         for (int t = threadIdx.x; t < tiles_v; t += 256) hist[t] = 0u;
     GroupRegs cur, nxt;
-    int64_t base = (int64_t)blockIdx.x * a.chunk_mult * GSR_BIN_CHUNK;
+    int64_t base = (int64_t)blockIdx.x * per_chunk;
     fetch_group(a, v, base, len, false, nxt);
     for (int sub = 0; sub < a.chunk_mult; ++sub, base += GSR_BIN_CHUNK) {
         if (base >= (int64_t)len) break;
@@ -366,76 +383,85 @@ __global__ void k_zero_u32(uint32_t* p, int64_t count)
         p[i] = 0u;
 }
 
-// Column scan: a block takes 64 consecutive global tiles; its wave s takes
-// the s-th quarter of every tile's chunks (so a wave reads 64 adjacent
-// counters of one row at a time).  Each wave sums its quarter of the
-// column, the quarters' sums give each quarter its offset, and the wave
-// rewrites its quarter as the exclusive prefix over chunks; the column's
-// total goes to ranges[].y.  32 loads are in flight at a time.
-__device__ __forceinline__ uint32_t colscan_run(uint32_t* col, int64_t stride, int c0, int c1, bool write,
-                                                uint32_t run)
+// Column scan: a block takes GSR_COL_TILES (32: a cache line of counters)
+// consecutive global tiles and scans their columns 256 chunks at a time, 32
+// groups of threads with 8 rows each: the rows are read once into registers
+// (the next pass's reads are issued before this one's barrier), the groups'
+// sums meet in LDS, and the rows are rewritten as the exclusive prefix over
+// chunks.  The column's total goes to ranges[].y.  Bound by the matrix's one
+// read and one write; with 64 tiles a block, four waves and two reads the
+// scan of one 1200x680 view (1954 chunks of 3225 tiles) kept 204 waves on 51
+// CUs busy for 40 us, now (half the chunks, too) 18; five such views 92 -> 43,
+// 36 views of 3M Gaussians 263 -> 98.
+__global__ __launch_bounds__(1024) void k_bin_colscan(BinArgs a)
 {
-    constexpr int K = 32;
-    int c = c0;
-    for (; c + K <= c1; c += K) {
-        uint32_t x[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) x[k] = col[(int64_t)(c + k) * stride];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (write) col[(int64_t)(c + k) * stride] = run;
-            run += x[k];
-        }
-    }
-    for (; c < c1; ++c) {
-        const uint32_t x = col[(int64_t)c * stride];
-        if (write) col[(int64_t)c * stride] = run;
-        run += x;
-    }
-    return run;
-}
-
-__global__ __launch_bounds__(256) void k_bin_colscan(BinArgs a)
-{
-    __shared__ uint32_t part[4][64];
-    const int lt = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int g = blockIdx.x * 64 + lt;
+    constexpr int K = 8, GROUPS = 1024 / GSR_COL_TILES;
+    static_assert(GSR_COL_TILES == 32, "the totals' scan runs over half a wave");
+    __shared__ uint32_t part[GROUPS][GSR_COL_TILES];
+    __shared__ int chunks_max;
+    const int lt = threadIdx.x & (GSR_COL_TILES - 1), q = threadIdx.x / GSR_COL_TILES;
+    const int g = blockIdx.x * GSR_COL_TILES + lt;
     const bool in = g < a.total_tiles;
     uint32_t* col = nullptr;
     int64_t stride = 0;
-    int c0 = 0, c1 = 0;
+    int chunks_v = 0;
+    if (threadIdx.x == 0) chunks_max = 0;
+    __syncthreads();
     if (in) {
         const int v = view_of_tile(a.views, g);
         const ViewInfo& vw = a.views->v[v];
         stride = (int64_t)vw.tiles_x * vw.tiles_y;
         col = a.cnt + (int64_t)a.chunks * vw.tile_base + (g - vw.tile_base);
-        const int chunks_v = view_chunks(a, v);
-        const int per = (chunks_v + 3) / 4;
-        c0 = min(q * per, chunks_v);
-        c1 = min(c0 + per, chunks_v);
+        chunks_v = view_chunks(a, v);
+        if (q == 0) atomicMax(&chunks_max, chunks_v);
     }
-    const uint32_t sum = in ? colscan_run(col, stride, c0, c1, false, 0u) : 0u;
-    part[q][lt] = sum;
     __syncthreads();
-    uint32_t off = 0u;
-    for (int k = 0; k < q; ++k) off += part[k][lt];
-    if (in) colscan_run(col, stride, c0, c1, true, off);
-    if (q == 3) {
-        // the last wave holds the 64 tiles' totals: their exclusive prefix
-        // within the block goes to ranges[].x, the block's pairs to
-        // tile_blocks (k_bin_tiles adds the earlier blocks')
-        const uint32_t total = off + sum;
-        unsigned long long incl = total;
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long y = __shfl_up(incl, o, 64);
+    const int last = chunks_max;
+    uint32_t carry = 0u, x[K], nx[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) nx[k] = q * K + k < chunks_v ? col[(int64_t)(q * K + k) * stride] : 0u;
+    for (int c0 = 0; c0 < last; c0 += K * GROUPS) {
+        uint32_t sum = 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            x[k] = nx[k];
+            sum += x[k];
+        }
+        const int c = c0 + q * K, cn = c + K * GROUPS;
+#pragma unroll
+        for (int k = 0; k < K; ++k) nx[k] = cn + k < chunks_v ? col[(int64_t)(cn + k) * stride] : 0u;
+        part[q][lt] = sum;
+        __syncthreads();
+        uint32_t run = carry, total = 0u;
+#pragma unroll
+        for (int k = 0; k < GROUPS; ++k) {
+            const uint32_t y = part[k][lt];
+            run += k < q ? y : 0u;
+            total += y;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (c + k < chunks_v) col[(int64_t)(c + k) * stride] = run;
+            run += x[k];
+        }
+        carry += total;
+        __syncthreads();
+    }
+    if (q == 0) {
+        // the 32 tiles' totals: their exclusive prefix within the block goes
+        // to ranges[].x, the block's pairs to tile_blocks (k_bin_tiles adds
+        // the earlier blocks')
+        unsigned long long incl = carry;
+        for (int o = 1; o < GSR_COL_TILES; o <<= 1) {
+            const unsigned long long y = __shfl_up(incl, o, GSR_COL_TILES);
             if (lt >= o) incl += y;
         }
-        if (in) a.ranges[g] = make_uint2((uint32_t)(incl - total), total);
-        if (lt == 63) a.tile_blocks[blockIdx.x] = incl;
+        if (in) a.ranges[g] = make_uint2((uint32_t)(incl - carry), carry);
+        if (lt == GSR_COL_TILES - 1) a.tile_blocks[blockIdx.x] = incl;
     }
 }
 
-// the tile ranges: each tile's start is the pairs of the earlier 64-tile
+// the tile ranges: each tile's start is the pairs of the earlier 32-tile
 // blocks plus its prefix within its block; the pair count and the capacity
 // flag come from the blocks' sum (every block forms it, so that all decide
 // the overflow alike)
@@ -443,8 +469,8 @@ __global__ __launch_bounds__(256) void k_bin_tiles(BinArgs a)
 {
     __shared__ unsigned long long red[2][4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int nb = (a.total_tiles + 63) / 64;
-    const int b0 = (int)blockIdx.x * 4;
+    const int nb = (a.total_tiles + GSR_COL_TILES - 1) / GSR_COL_TILES;
+    const int b0 = (int)blockIdx.x * (256 / GSR_COL_TILES);
     unsigned long long pre = 0ull, tot = 0ull;
     for (int k = tid; k < nb; k += 256) {
         const unsigned long long x = a.tile_blocks[k];
@@ -465,7 +491,7 @@ __global__ __launch_bounds__(256) void k_bin_tiles(BinArgs a)
     const bool over = tot > a.counters->capacity;
     const int g = (int)blockIdx.x * 256 + tid;
     if (g < a.total_tiles) {
-        for (int k = b0; k < b0 + w; ++k) pre += a.tile_blocks[k];
+        for (int k = b0; k < b0 + tid / GSR_COL_TILES; ++k) pre += a.tile_blocks[k];
         const uint2 r = a.ranges[g];
         const unsigned long long start = pre + r.x;
         // empty tiles get [0, 0); on overflow every range is empty, so that
@@ -492,7 +518,8 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a)
     const int per = (nc + GSR_XCDS - 1) / GSR_XCDS;
     const int chunk = (int)(blockIdx.x % GSR_XCDS) * per + (int)(blockIdx.x / GSR_XCDS);
     if ((int)(blockIdx.x / GSR_XCDS) >= per || chunk >= nc) return;
-    const uint32_t len = live_len(a, v);
+    const uint32_t live = live_len(a, v), per_chunk = chunk_len(a, live);
+    const uint32_t len = min(live, ((uint32_t)chunk + 1u) * per_chunk);  // the chunk's end
     const ViewInfo vw = a.views->v[v];
     const int tiles_v = vw.tiles_x * vw.tiles_y;
     uint32_t* row = count_row(a, vw, chunk);
@@ -500,7 +527,7 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a)
     if (LDS_HIST)
         for (int t = threadIdx.x; t < tiles_v; t += 256) cursor[t] = rng[t].x + row[t];
     GroupRegs cur, nxt;
-    int64_t base = (int64_t)chunk * a.chunk_mult * GSR_BIN_CHUNK;
+    int64_t base = (int64_t)chunk * per_chunk;
     fetch_group(a, v, base, len, true, nxt);
     for (int sub = 0; sub < a.chunk_mult; ++sub, base += GSR_BIN_CHUNK) {
         if (base >= (int64_t)len) break;
@@ -547,7 +574,8 @@ hipError_t launch_bin(const BinArgs& a, int max_tiles_view, hipStream_t s)
         hipLaunchKernelGGL(k_zero_u32, dim3(2048), dim3(256), 0, s, a.cnt, entries);
         hipLaunchKernelGGL(k_bin_count<false>, grid, dim3(256), 0, s, a);
     }
-    hipLaunchKernelGGL(k_bin_colscan, dim3((unsigned)((a.total_tiles + 63) / 64)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_bin_colscan, dim3((unsigned)((a.total_tiles + GSR_COL_TILES - 1) / GSR_COL_TILES)), dim3(1024), 0,
+                       s, a);
     hipLaunchKernelGGL(k_bin_tiles, dim3((unsigned)((a.total_tiles + 255) / 256)), dim3(256), 0, s, a);
     if (lds) hipLaunchKernelGGL(k_bin_emit<true>, grid, dim3(256), dyn, s, a);
     else hipLaunchKernelGGL(k_bin_emit<false>, grid, dim3(256), 0, s, a);

@@ -228,13 +228,17 @@ extern "C" gsr_status gsr_plan_create(int64_t n, int32_t n_views, const gsr_came
     // binning chunks of GSR_BIN_CHUNK * chunk_mult live slots per block (the
     // slots of a view whose tile rectangle is not empty, listed by the
     // binning's first pass).  Each block writes a count row of its view's
-    // tiles; one staged group per block measured best on MI355X (larger
-    // chunks shorten the count matrix but leave fewer, longer blocks).  The
-    // grid is sized for a view whose every slot is live, and blocks past a
-    // view's live count exit at once
+    // tiles; two staged groups per block measured best on MI355X (one: the
+    // count matrix of five 1200x680 views of 500k live Gaussians costs counting,
+    // scan and emission 97 us more than the 165 they take; four: the ten views
+    // of 1M, of uneven sizes, 645 us for 537).  The grid is sized for a view
+    // whose every slot is live, and blocks past a view's live count exit at
+    // once
     p->chunk_mult = GSR_BIN_CHUNK_MULT;
-    p->chunks = (int32_t)std::max<int64_t>(
-        1, (n + (int64_t)GSR_BIN_CHUNK * p->chunk_mult - 1) / ((int64_t)GSR_BIN_CHUNK * p->chunk_mult));
+    // (and rows enough for a sparse view's smaller chunks)
+    const int64_t full = (int64_t)GSR_BIN_CHUNK * p->chunk_mult;
+    const int64_t least = std::min<int64_t>((n + GSR_BIN_LEAST - 1) / GSR_BIN_LEAST, GSR_BIN_BLOCKS / n_views);
+    p->chunks = (int32_t)std::max<int64_t>({1, (n + full - 1) / full, least});
     p->bwd_blocks = (int32_t)((n + 255) / 256);
     if (p->bwd_blocks == 0) p->bwd_blocks = 1;
 
@@ -267,7 +271,7 @@ extern "C" gsr_status gsr_plan_create(int64_t n, int32_t n_views, const gsr_came
     p->off_live = take(sizeof(uint32_t) * S);
 
     p->off_live_count = take(sizeof(uint32_t) * GSR_LIVE_STRIDE * GSR_MAX_VIEWS);  // one 256-byte line per view
-    p->off_tile_blocks = take(sizeof(unsigned long long) * (size_t)((p->total_tiles + 63) / 64 + 1));
+    p->off_tile_blocks = take(sizeof(unsigned long long) * (size_t)((p->total_tiles + GSR_COL_TILES - 1) / GSR_COL_TILES + 1));
     p->off_xip = take(sizeof(double) * 6 * (size_t)n_views * p->bwd_blocks);
     p->off_xip_sh = take(sizeof(double) * 6 * (size_t)n_views * p->bwd_blocks);
     p->off_track = take(sizeof(double) * GSR_TRACK_SLOTS * GSR_TRACK_BLOCKS * (size_t)n_views);

@@ -41,7 +41,7 @@ struct BinArgs {
     Counters* counters;
     uint2* ranges;             // [total_tiles]: [first, last + 1) of each tile's pairs
     unsigned long long* seg;   // [capacity]: (depth bits << 32 | Gaussian index), grouped by tile
-    unsigned long long* tile_blocks;  // [ceil(total_tiles / 64)]: pairs of each run of 64 tiles
+    unsigned long long* tile_blocks;  // [ceil(total_tiles / GSR_COL_TILES)]: pairs of each run of that many tiles
 };
 
 struct SegArgs {
@@ -283,8 +283,15 @@ struct FrameArgs {
 #define GSR_TRACK_SLOTS 8           // partial sums per block (4 exposure sums, 3 loss/sign sums)
 #define GSR_BIN_CHUNK 256           // Gaussians staged in LDS at a time by the binning blocks (x256)
 #define GSR_BIN_LDS_TILES 16384     // views with more tiles count and place with global atomics
+#define GSR_COL_TILES 32            // tiles per block of the count matrix's column scan
+#ifndef GSR_BIN_LEAST
+#define GSR_BIN_LEAST 64            // least live slots of a chunk
+#endif
+#ifndef GSR_BIN_BLOCKS
+#define GSR_BIN_BLOCKS 512          // chunks below which they are made smaller
+#endif
 #ifndef GSR_BIN_CHUNK_MULT
-#define GSR_BIN_CHUNK_MULT 1        // live slots per binning chunk, in units of GSR_BIN_CHUNK
+#define GSR_BIN_CHUNK_MULT 2        // live slots per binning chunk, in units of GSR_BIN_CHUNK
 #endif
 #define GSR_LIVE_STRIDE 64          // uint32 between two views' live counters (one 256-byte line each)
 #define GSR_XCDS 8                  // accelerator dies; workgroups are dealt to them in turn
