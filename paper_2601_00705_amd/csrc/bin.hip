@@ -282,20 +282,31 @@ __device__ __forceinline__ void walk_group(const ChunkLds& L, const Staged& st, 
     }
 }
 
-#define GSR_LIST_WORDS 2  // ballot words per thread of k_bin_list
+// the views' live counts and the processing order's bucket counts and cursors
+__global__ __launch_bounds__(64) void k_bin_zero(BinArgs a)
+{
+    if (threadIdx.x == 0) a.live_count[blockIdx.x * GSR_LIVE_STRIDE] = 0u;
+    if (blockIdx.x == 0) a.buckets[threadIdx.x] = 0u;
+}
 
+// Every wave holds the block's 64 WORDS ballot words (WORDS to a lane) and
+// their prefix, and writes a quarter of them: 16 to a wave for one word a lane
+// (128, at two words a lane and every wave its own, took 9 us at any size
+// below 500k Gaussians, four blocks at 100k; now 5).  Past a million Gaussians
+// the blocks' atomics on the view's counter would queue (36 views of 3M: 71
+// us), so a lane takes four.
+template <int WORDS>
 __global__ __launch_bounds__(256) void k_bin_list(BinArgs a)
 {
-    __shared__ uint32_t wsum[4];
     __shared__ uint32_t base_s;
     const int v = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t w0 = ((int64_t)blockIdx.x * 256 + tid) * GSR_LIST_WORDS;
-    uint64_t m[GSR_LIST_WORDS];
+    const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6);
+    const int64_t w0 = (int64_t)blockIdx.x * 64 * WORDS;
+    uint64_t m[WORDS];
     uint32_t cnt = 0;
 #pragma unroll
-    for (int k = 0; k < GSR_LIST_WORDS; ++k) {
-        const int64_t wd = w0 + k;
+    for (int k = 0; k < WORDS; ++k) {
+        const int64_t wd = w0 + lane * WORDS + k;
         m[k] = wd < a.mask_words ? a.live_mask[wd * a.n_views + v] : 0ull;
         // no Gaussian past n
         if (wd == a.mask_words - 1 && (a.n & 63)) m[k] &= (1ull << (a.n & 63)) - 1ull;
@@ -306,31 +317,23 @@ __global__ __launch_bounds__(256) void k_bin_list(BinArgs a)
         const uint32_t y = __shfl_up(incl, off, 64);
         if (lane >= off) incl += y;
     }
-    if (lane == 63) wsum[w] = incl;
+    if (threadIdx.x == 63) base_s = incl ? atomicAdd(&a.live_count[v * GSR_LIVE_STRIDE], incl) : 0u;
     __syncthreads();
-    if (tid == 0) {
-        const uint32_t total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        base_s = total ? atomicAdd(&a.live_count[v * GSR_LIVE_STRIDE], total) : 0u;
-    }
-    __syncthreads();
-    uint32_t pos = base_s + incl - cnt;
-    for (int k = 0; k < w; ++k) pos += wsum[k];
+    const uint32_t pos = base_s + incl - cnt;
     uint32_t* list = a.live + (int64_t)v * a.n;
-    // the wave writes its words' entries together, one word at a time: lane
-    // l keeps bit l of the word, so the set bits go out as one coalesced run
-    // (in index order, as a thread would write them)
+    // a word's entries go out together: lane l keeps bit l of the word, so
+    // the set bits are one coalesced run in index order
     const uint64_t below = (1ull << lane) - 1ull;
-    for (int j = 0; j < 64; ++j) {
+    for (int t = 0; t < 16; ++t) {
+        const int j = w * 16 + t;
         uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)pos, j);
 #pragma unroll
-        for (int k = 0; k < GSR_LIST_WORDS; ++k) {
+        for (int k = 0; k < WORDS; ++k) {
             const uint64_t word = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(m[k] >> 32), j) << 32) |
                                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m[k], j);
             if (word == 0ull) continue;
-            if ((word >> lane) & 1ull) {
-                const int64_t wd = (int64_t)(blockIdx.x * 256 + w * 64 + j) * GSR_LIST_WORDS + k;
-                list[at + (uint32_t)__popcll(word & below)] = (uint32_t)(wd * 64 + lane);
-            }
+            if ((word >> lane) & 1ull)
+                list[at + (uint32_t)__popcll(word & below)] = (uint32_t)((w0 + j * WORDS + k) * 64 + lane);
             at += (uint32_t)__popcll(word);
         }
     }
@@ -461,16 +464,27 @@ __global__ __launch_bounds__(1024) void k_bin_colscan(BinArgs a)
     }
 }
 
-// the tile ranges: each tile's start is the pairs of the earlier 32-tile
+// The tile ranges: each tile's start is the pairs of the earlier 32-tile
 // blocks plus its prefix within its block; the pair count and the capacity
 // flag come from the blocks' sum (every block forms it, so that all decide
-// the overflow alike)
+// the overflow alike).  The tiles are also counted into the processing
+// order's buckets.
+__device__ __forceinline__ uint2 tile_range_of(uint2 r, unsigned long long pre, bool over)
+{
+    // empty tiles get [0, 0); on overflow every range is empty, so that no
+    // kernel reads past the capacity
+    const unsigned long long start = pre + r.x;
+    return (over || r.y == 0u) ? make_uint2(0u, 0u) : make_uint2((uint32_t)start, (uint32_t)(start + r.y));
+}
+
 __global__ __launch_bounds__(256) void k_bin_tiles(BinArgs a)
 {
     __shared__ unsigned long long red[2][4];
+    __shared__ uint32_t hist[32];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int nb = (a.total_tiles + GSR_COL_TILES - 1) / GSR_COL_TILES;
     const int b0 = (int)blockIdx.x * (256 / GSR_COL_TILES);
+    if (tid < 32) hist[tid] = 0u;
     unsigned long long pre = 0ull, tot = 0ull;
     for (int k = tid; k < nb; k += 256) {
         const unsigned long long x = a.tile_blocks[k];
@@ -492,16 +506,71 @@ __global__ __launch_bounds__(256) void k_bin_tiles(BinArgs a)
     const int g = (int)blockIdx.x * 256 + tid;
     if (g < a.total_tiles) {
         for (int k = b0; k < b0 + tid / GSR_COL_TILES; ++k) pre += a.tile_blocks[k];
-        const uint2 r = a.ranges[g];
-        const unsigned long long start = pre + r.x;
-        // empty tiles get [0, 0); on overflow every range is empty, so that
-        // no kernel reads past the capacity
-        a.ranges[g] = (over || r.y == 0u) ? make_uint2(0u, 0u)
-                                          : make_uint2((uint32_t)start, (uint32_t)(start + r.y));
+        const uint2 r = tile_range_of(a.ranges[g], pre, over);
+        a.ranges[g] = r;
+        atomicAdd(&hist[count_bucket(r)], 1u);
     }
     if (blockIdx.x == 0 && tid == 0) {
         a.counters->pairs = tot;
         a.counters->overflow = over ? 1u : 0u;
+    }
+    __syncthreads();
+    if (tid < 32 && hist[tid]) atomicAdd(&a.buckets[tid], hist[tid]);
+}
+
+// The same for at most GSR_ONE_TILES tiles, in one block, which also places
+// them in the processing order: instead of this, k_order_count and
+// k_order_place, each 4 to 5 us of a 242 us step.
+__global__ __launch_bounds__(1024) void k_bin_tiles_one(BinArgs a)
+{
+    constexpr int PER = GSR_ONE_TILES / 1024, NB = GSR_ONE_TILES / GSR_COL_TILES;
+    static_assert(NB == 128, "the blocks' sums are scanned by two waves");
+    __shared__ unsigned long long base[NB], half;
+    __shared__ uint32_t hist[32], cursor[32];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int nb = (a.total_tiles + GSR_COL_TILES - 1) / GSR_COL_TILES;
+    if (tid < 32) hist[tid] = 0u;
+    unsigned long long incl = 0ull, own = 0ull;
+    if (tid < NB) {
+        own = incl = tid < nb ? a.tile_blocks[tid] : 0ull;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (tid == 63) half = incl;
+    }
+    __syncthreads();
+    if (tid < NB) base[tid] = incl - own + (tid < 64 ? 0ull : half);
+    __syncthreads();
+    const unsigned long long tot = base[nb - 1] + a.tile_blocks[nb - 1];
+    const bool over = tot > a.counters->capacity;
+    uint32_t bucket[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int g = tid + k * 1024;
+        bucket[k] = 0u;
+        if (g < a.total_tiles) {
+            const uint2 r = tile_range_of(a.ranges[g], base[g / GSR_COL_TILES], over);
+            a.ranges[g] = r;
+            bucket[k] = count_bucket(r);
+            atomicAdd(&hist[bucket[k]], 1u);
+        }
+    }
+    if (tid == 0) {
+        a.counters->pairs = tot;
+        a.counters->overflow = over ? 1u : 0u;
+    }
+    __syncthreads();
+    if (tid < 32) {
+        uint32_t run = 0;
+        for (int k = 0; k < tid; ++k) run += hist[k];
+        cursor[tid] = run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int g = tid + k * 1024;
+        if (g < a.total_tiles) a.order[atomicAdd(&cursor[bucket[k]], 1u)] = (uint32_t)g;
     }
 }
 
@@ -558,12 +627,11 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a)
 hipError_t launch_bin(const BinArgs& a, int max_tiles_view, hipStream_t s)
 {
     if (a.total_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_u32, dim3(16), dim3(256), 0, s, a.live_count, (int64_t)GSR_LIVE_STRIDE * GSR_MAX_VIEWS);
-    const int64_t per_block = 256 * GSR_LIST_WORDS;
-    hipLaunchKernelGGL(k_bin_list,
-                       dim3((unsigned)std::max<int64_t>((a.mask_words + per_block - 1) / per_block, 1),
-                            (unsigned)a.n_views),
-                       dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_bin_zero, dim3((unsigned)a.n_views), dim3(64), 0, s, a);
+    const int words = a.mask_words > 16384 ? 4 : 1;
+    const dim3 lists((unsigned)std::max<int64_t>((a.mask_words + 64 * words - 1) / (64 * words), 1), (unsigned)a.n_views);
+    if (words == 4) hipLaunchKernelGGL(k_bin_list<4>, lists, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_bin_list<1>, lists, dim3(256), 0, s, a);
     dim3 grid((unsigned)((a.chunks + GSR_XCDS - 1) / GSR_XCDS * GSR_XCDS), (unsigned)a.n_views);
     const bool lds = max_tiles_view <= GSR_BIN_LDS_TILES;
     const size_t dyn = lds ? sizeof(uint32_t) * (size_t)max_tiles_view : 0;
@@ -576,7 +644,8 @@ hipError_t launch_bin(const BinArgs& a, int max_tiles_view, hipStream_t s)
     }
     hipLaunchKernelGGL(k_bin_colscan, dim3((unsigned)((a.total_tiles + GSR_COL_TILES - 1) / GSR_COL_TILES)), dim3(1024), 0,
                        s, a);
-    hipLaunchKernelGGL(k_bin_tiles, dim3((unsigned)((a.total_tiles + 255) / 256)), dim3(256), 0, s, a);
+    if (a.total_tiles <= GSR_ONE_TILES) hipLaunchKernelGGL(k_bin_tiles_one, dim3(1), dim3(1024), 0, s, a);
+    else hipLaunchKernelGGL(k_bin_tiles, dim3((unsigned)((a.total_tiles + 255) / 256)), dim3(256), 0, s, a);
     if (lds) hipLaunchKernelGGL(k_bin_emit<true>, grid, dim3(256), dyn, s, a);
     else hipLaunchKernelGGL(k_bin_emit<false>, grid, dim3(256), 0, s, a);
     return hipGetLastError();

@@ -449,6 +449,8 @@ extern "C" gsr_status gsr_bin(gsr_plan* plan, void* stream)
     b.counters = at<Counters>(plan, plan->off_counters);
     b.ranges = at<uint2>(plan, plan->off_ranges);
     b.seg = at<unsigned long long>(plan, plan->off_seg);
+    b.order = at<uint32_t>(plan, plan->off_order);
+    b.buckets = at<uint32_t>(plan, plan->off_buckets);
     RangeArgs r{};
     r.counters = b.counters;
     r.ranges = b.ranges;

@@ -146,6 +146,14 @@ __device__ __forceinline__ int view_of_tile(const ViewTable* vt, int tile)
     return v;
 }
 
+// bucket of the tiles' processing order: 31 - floor(log2(pairs)), 31 when
+// empty (bucket 0 holds the longest lists)
+__device__ __forceinline__ uint32_t count_bucket(uint2 r)
+{
+    const uint32_t c = r.y - r.x;
+    return c == 0u ? 31u : (uint32_t)__clz(c);
+}
+
 // ---------------------------------------------------------------------------
 // wave64 cross-lane helpers on VALU instructions (no LDS round trip):
 // v_permlane32_swap / v_permlane16_swap exchange lane i with lane i ^ 32 /

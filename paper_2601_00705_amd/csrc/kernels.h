@@ -42,6 +42,8 @@ struct BinArgs {
     uint2* ranges;             // [total_tiles]: [first, last + 1) of each tile's pairs
     unsigned long long* seg;   // [capacity]: (depth bits << 32 | Gaussian index), grouped by tile
     unsigned long long* tile_blocks;  // [ceil(total_tiles / GSR_COL_TILES)]: pairs of each run of that many tiles
+    uint32_t* order;           // [tiles]: tiles by pair count, descending (few tiles)
+    uint32_t* buckets;         // [64]: tiles per log2 bucket, then cursors
 };
 
 struct SegArgs {
@@ -283,6 +285,7 @@ struct FrameArgs {
 #define GSR_TRACK_SLOTS 8           // partial sums per block (4 exposure sums, 3 loss/sign sums)
 #define GSR_BIN_CHUNK 256           // Gaussians staged in LDS at a time by the binning blocks (x256)
 #define GSR_BIN_LDS_TILES 16384     // views with more tiles count and place with global atomics
+#define GSR_ONE_TILES 4096          // most tiles whose ranges and order one block forms
 #define GSR_COL_TILES 32            // tiles per block of the count matrix's column scan
 #ifndef GSR_BIN_LEAST
 #define GSR_BIN_LEAST 64            // least live slots of a chunk

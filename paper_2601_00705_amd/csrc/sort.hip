@@ -4,8 +4,9 @@
 //              64-bit keys (depth bits << 32 | Gaussian index) ascending and
 //              writes the final pairs: key (tile << 32 | depth bits), value
 //              slot = view * n + index.
-// k_order_*    processing order of the tiles: descending pair count, bucketed
-//              by floor(log2(count)), for the segment sort and compositing.
+// k_order_place  processing order of the tiles: descending pair count,
+//              bucketed by floor(log2(count)), for the segment sort and
+//              compositing (few tiles are placed where their ranges are formed).
 //
 // A list is placed, not ranked digit by digit: a histogram of its depth bits
 // over GSR_SEG_COARSE linear bins gives its depth distribution, every coarse
@@ -584,29 +585,7 @@ hipError_t launch_seg_sort(const SegArgs& a, int total_tiles, hipStream_t s)
 
 // ---------------------------------------------------------------------------
 // processing order of the tiles: descending pair count, bucketed by
-// floor(log2(count)) (bucket 0 holds the longest lists)
-
-__device__ __forceinline__ uint32_t count_bucket(uint2 r)
-{
-    uint32_t c = r.y - r.x;
-    return c == 0u ? 31u : (uint32_t)__clz(c);  // 31 - floor(log2 c)
-}
-
-__global__ void k_order_zero(RangeArgs a)
-{
-    if (threadIdx.x < 64) a.buckets[threadIdx.x] = 0u;
-}
-
-__global__ void k_order_count(RangeArgs a)
-{
-    __shared__ uint32_t h[32];
-    if (threadIdx.x < 32) h[threadIdx.x] = 0u;
-    __syncthreads();
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < a.total_tiles) atomicAdd(&h[count_bucket(a.ranges[t])], 1u);
-    __syncthreads();
-    if (threadIdx.x < 32 && h[threadIdx.x]) atomicAdd(&a.buckets[threadIdx.x], h[threadIdx.x]);
-}
+// floor(log2(count)) (count_bucket; counted with the tile ranges)
 
 // places each tile at its bucket's base plus a block-aggregated cursor: one
 // global atomic per (block, bucket)
@@ -636,11 +615,8 @@ __global__ void k_order_place(RangeArgs a)
 
 hipError_t launch_order(const RangeArgs& a, hipStream_t s)
 {
-    if (a.total_tiles == 0) return hipSuccess;
-    const int tb = (a.total_tiles + 255) / 256;
-    hipLaunchKernelGGL(k_order_zero, dim3(1), dim3(64), 0, s, a);
-    hipLaunchKernelGGL(k_order_count, dim3(tb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_order_place, dim3(tb), dim3(256), 0, s, a);
+    if (a.total_tiles <= GSR_ONE_TILES) return hipSuccess;  // placed by k_bin_tiles_one
+    hipLaunchKernelGGL(k_order_place, dim3((unsigned)((a.total_tiles + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

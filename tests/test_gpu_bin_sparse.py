@@ -16,7 +16,8 @@ if torch.cuda.is_available():
 
 
 @pytest.mark.parametrize("n,live", [(1, 1), (70, 63), (70, 64), (70, 65), (3000, 0), (3000, 129), (3000, 3000),
-                                    (40000, 257), (40000, 16385), (40000, 40000), (140000, 140000)])
+                                    (40000, 257), (40000, 16385), (40000, 40000), (140000, 140000),
+                                    (1100000, 1100000)])
 @pytest.mark.parametrize("views", [1, 3])
 def test_sparse(n, live, views):
     print(f"[sparse] n={n} live={live} views={views}", flush=True)
@@ -27,7 +28,7 @@ def test_sparse(n, live, views):
     for v in range(views):  # all but `live` of the view's Gaussians are culled
         dead = rng.permutation(n)[live:]
         recs[2][v * n + dead] = -1.0
-    R = Renderer(n, cams, Config(), pair_capacity=4_000_000)
+    R = Renderer(n, cams, Config(), pair_capacity=40_000_000)
     M, overflow = _fill_and_bin(R, recs)
     assert not overflow
     keys, vals, ranges = R.sorted_pairs(M)
