@@ -1169,7 +1169,7 @@ extern "C" gsr_status gsr_compact(int64_t n, int32_t rows, const float* src, con
 // partials, digit totals, each on a 256-byte boundary
 static size_t order_layout(int64_t n, size_t off[7])
 {
-    const int64_t blocks = (n + GSR_RADIX_TILE - 1) / GSR_RADIX_TILE;
+    const int64_t blocks = (n + radix_tile(n) - 1) / radix_tile(n);
     size_t at = 0;
     auto take = [&](size_t bytes) {
         const size_t o = at;
@@ -1234,7 +1234,8 @@ extern "C" gsr_status gsr_spatial_order(int64_t n, const float* mean, int32_t br
     a.hist = (uint32_t*)(base + off[4]);
     a.box = (uint32_t*)(base + off[5]);
     a.tot = (uint32_t*)(base + off[6]);
-    a.blocks = (int32_t)((n + GSR_RADIX_TILE - 1) / GSR_RADIX_TILE);
+    a.tile = (int32_t)radix_tile(n);
+    a.blocks = (int32_t)((n + a.tile - 1) / a.tile);
     a.brick = brick;
     a.full = n / brick;
     a.mult = brick_multiplier(a.full);

@@ -6,7 +6,12 @@
 
 namespace gsr {
 
-#define GSR_RADIX_TILE 4096  // keys per block of a radix pass (256 threads x 16)
+// keys per block of a radix pass: 1024 (four rounds of 256 threads), or 4096
+// past GSR_RADIX_SMALL keys, where the blocks' counts would outgrow their scan.
+// A pass's scatter at 30,011 keys took 15.6 us with 8 blocks of 4096, now 6.6
+// with 30 of 1024; at 1M 17.5 and 10.5.
+#define GSR_RADIX_SMALL (1 << 20)
+static inline int64_t radix_tile(int64_t n) { return n <= GSR_RADIX_SMALL ? 1024 : 4096; }
 #define GSR_RADIX_BITS 8     // digit width; four passes cover the 31-bit codes
 #define GSR_BOX_BLOCKS 256   // blocks of the box pass, one partial box each
 
@@ -20,7 +25,8 @@ struct OrderArgs {
     uint32_t* val[2];    // [n] each: Gaussian indices, ping-pong
     uint32_t* hist;      // [256][blocks]: per-block digit counts, then their offsets within the digit
     uint32_t* tot;       // [256]: keys per digit of the pass
-    int32_t blocks;      // radix tiles of GSR_RADIX_TILE keys
+    int32_t blocks;      // radix tiles
+    int32_t tile;        // radix_tile(n) keys each
     int32_t brick;
     int64_t full;        // n / brick
     int64_t mult;        // the brick multiplier P

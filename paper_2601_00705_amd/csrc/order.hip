@@ -168,10 +168,10 @@ __global__ __launch_bounds__(256) void k_radix_hist(OrderArgs a, int src, int sh
     const int tid = threadIdx.x;
     h[tid] = 0u;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * GSR_RADIX_TILE;
+    const int64_t base = (int64_t)blockIdx.x * a.tile;
     const uint32_t* code = a.code[src];
 #pragma unroll 4
-    for (int k = 0; k < GSR_RADIX_TILE / 256; ++k) {
+    for (int k = 0; k < a.tile / 256; ++k) {
         const int64_t i = base + k * 256 + tid;
         if (i < a.n) atomicAdd(&h[(code[i] >> shift) & 255u], 1u);
     }
@@ -232,13 +232,13 @@ __global__ __launch_bounds__(256) void k_radix_scatter(OrderArgs a, int src, int
         goff[tid] = start + a.hist[(int64_t)tid * a.blocks + blockIdx.x];
     }
     run[tid] = 0u;
-    const int64_t base = (int64_t)blockIdx.x * GSR_RADIX_TILE;
+    const int64_t base = (int64_t)blockIdx.x * a.tile;
     const uint32_t* code_in = a.code[src];
     const uint32_t* val_in = a.val[src];
     uint32_t* code_out = a.code[src ^ 1];
     uint32_t* val_out = a.val[src ^ 1];
     const uint64_t below = (1ull << lane) - 1ull;
-    for (int k = 0; k < GSR_RADIX_TILE / 256; ++k) {
+    for (int k = 0; k < a.tile / 256; ++k) {
         for (int d = lane; d < 256; d += 64) wc[w][d] = 0u;
         const int64_t i = base + k * 256 + tid;
         const bool valid = i < a.n;
