@@ -293,7 +293,7 @@ def maintenance_measurement(torch, w, params, T_final, cams, reps, log):
             indices written (8 B), four radix passes each reading them twice
             and writing them once (4 x 24 B), the brick gather (8 B), then
             every row gathered (12 B per row: index, read, write).
-    The nearest-neighbour search before merging is a grid search, reported
+    The nearest-neighbour search before merging walks a tree, reported
     by its time only."""
     import numpy as np
     from paper_2601_00705_amd import maintain

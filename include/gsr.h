@@ -213,14 +213,11 @@ gsr_status gsr_project(gsr_plan *plan, const gsr_gaussians *g, const float *pose
  * d^T conic d <= qthr).  gsr_project writes the records and the mask; a
  * caller that writes records itself also sets the mask bit of every slot
  * with a non-empty rectangle (other bits add no pair):
- * pair emission, stable LSD radix sort of (tile | depth) keys with slot
- * values, tile ranges.  When the pair count exceeds the capacity, a device
+ * pair counts, tile ranges, pair emission, per-tile sort by (depth bits,
+ * Gaussian index).  When the pair count exceeds the capacity, a device
  * flag is set, no pair is written, gsr_render_fwd writes NaN images and
- * gsr_render_bwd writes NaN gradients; gsr_pair_count reports it.  The sort
- * of segments longer than 8192 pairs runs on the plan's second stream,
- * forked from `stream` after the tile ranges and joined back before gsr_bin
- * returns its work to `stream` (the fork and join are recorded too when
- * `stream` is being captured into a graph). */
+ * gsr_render_bwd writes NaN gradients; gsr_pair_count reports it.  All work
+ * runs on `stream`. */
 gsr_status gsr_bin(gsr_plan *plan, void *stream);
 
 /* Eq. (alpha) for every view.  rgb, T_final, n_contrib required; n_blend
@@ -377,9 +374,9 @@ gsr_status gsr_seed_scale(int64_t n, const float *mean, const int32_t *valid, fl
  * unit quaternion (w, x, y, z) of U, and log_scale [3][n] = (log s_perp,
  * log s_perp, log s_par); the identity and zeros for invalid seeds.
  * workspace: gsr_seed_scale_workspace_bytes(n) bytes of device memory.
- * The search hashes the seeds by cells of `radius` and visits the 3 x 3 x 3
- * cells around each seed, so its cost grows with the number of seeds within
- * about two radii.  Bad arguments (n out of range, a non-positive or non-finite
+ * The search walks the leaves (64 seeds with their box) that come within
+ * `radius` of a seed, so its cost grows with the number of seeds within about
+ * that radius.  Bad arguments (n out of range, a non-positive or non-finite
  * radius, c_par or floor_scale, a non-finite P_ref or centre_ref, a null
  * buffer, a small workspace): GSR_EINVAL, nothing enqueued. */
 gsr_status gsr_seed_frame(int64_t n, const float *mean, const int32_t *valid, const float *err, const float *angle,

@@ -7,11 +7,12 @@
 //   (float bits of the camera depth << 32) | Gaussian index,
 // which orders a segment by depth and breaks ties by index (positive floats
 // order like their bit patterns).  The tile is the most significant part of
-// the order, so it is resolved by counting instead of sorting.  A chunk is
-// chunk_mult * GSR_BIN_CHUNK consecutive entries of one view's list of live
-// Gaussians (those whose rectangle is not empty), staged GSR_BIN_CHUNK at a
-// time:
+// the order, so it is resolved by counting instead of sorting.  A chunk is a
+// run of consecutive entries of one view's list of live Gaussians (those whose
+// rectangle is not empty), chunk_mult * GSR_BIN_CHUNK or fewer (chunk_len),
+// staged GSR_BIN_CHUNK at a time:
 //
+//   k_bin_zero    clears the views' live counts and the order's buckets
 //   k_bin_list    per view, the list of live Gaussians from the projection's
 //                 liveness ballots (a block scans its words' popcounts and
 //                 reserves its places with one atomic on the view's counter,
@@ -25,7 +26,9 @@
 //                 inside the tile's segment) and the tile's total, 32
 //                 groups of threads to a column
 //   k_bin_tiles   the tile ranges from the column scan's per-block prefixes
-//                 and block sums, the pair count and the capacity flag
+//                 and block sums, the pair count and the capacity flag, and
+//                 the tiles per bucket of the processing order
+//                 (k_bin_tiles_one: for few tiles, the order as well)
 //   k_bin_emit    the chunk's pairs, each at its tile's cursor (LDS atomics:
 //                 the order inside a chunk's group is arbitrary, and the
 //                 per-tile sort of the unique keys makes it exact)

@@ -61,7 +61,7 @@ struct gsr_plan {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> pending[GSR_T_COUNT];
     double timed_ms[GSR_T_COUNT] = {};
     int64_t timed_launches[GSR_T_COUNT] = {};
-    // the long-segment sort runs on a second stream of the plan, forked from
+    // the forward's longest tiles run on a second stream of the plan, forked from
     // and joined back to the caller's stream by two events (host objects,
     // created when the plan is bound; default stream priority)
     hipStream_t side = nullptr;

@@ -10,6 +10,9 @@
 // alpha_min test as power2 < log2(alpha_min / o)); then the lane walks the
 // batch for each of its pixels, sharing the per-entry terms of its column.
 //
+// Plans of few tiles deal a tile's pixels to several waves (k_raster_fwd_few,
+// k_raster_bwd_few), with the same arithmetic.
+//
 // Forward: alpha = min(alpha_max, o 2^power2); entries below alpha_min are
 // skipped; compositing stops before an entry that would take T below T_min;
 // out = C + T bg, plus T_final and n_contrib (list position + 1 of the last
