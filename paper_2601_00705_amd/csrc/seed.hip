@@ -51,11 +51,15 @@ __device__ void smallest_right_singular(double A[4][4], double out[4])
                 // its norms: below that the rounding of the dot products
                 // themselves dominates, and a stricter test never settles
                 // (every system would run to the sweep cap)
-                if (ga == 0.0 || fabs(ga) <= 1e-15 * sqrt(al * be)) continue;
+                if (ga == 0.0 || ga * ga <= 1e-30 * (al * be)) continue;
                 rotated = true;
-                const double zeta = (be - al) / (2.0 * ga);
-                const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                const double c = 1.0 / sqrt(1.0 + t * t), s = c * t;
+                // t = sgn(zeta) / (|zeta| + sqrt(1 + zeta^2)), zeta = d / (2 ga),
+                // with numerator and denominator times 2 |ga|: one root and
+                // one quotient, then one reciprocal root, instead of three of
+                // each (they are most of a rotation's instructions)
+                const double d = be - al, g2 = 2.0 * ga;
+                const double t = (d >= 0.0 ? g2 : -g2) / (fabs(d) + sqrt(d * d + g2 * g2));
+                const double c = rsqrt(1.0 + t * t), s = c * t;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const double ap = A[i][p], aq = A[i][q];
@@ -159,7 +163,9 @@ __device__ __forceinline__ Hypothesis hypothesis(const SeedArgs& a, int64_t i, i
 // Bound by the FP64 rotations where pixels fill the chip (500k, four
 // neighbours: 451 us at 1, 2 or 4 lanes a pixel alike), and by one pixel's
 // chain of them where they do not: 1000 pixels took 69 us with a lane each, 41
-// with two, 24 with four.
+// with two, 24 with four.  Half of a rotation was its three roots and three
+// quotients; with one root, one quotient and one reciprocal root these are
+// 370 and 20 us.
 template <int G>
 __global__ __launch_bounds__(GSR_SEED_THREADS) void k_seed_triangulate(SeedArgs a)
 {
