@@ -304,7 +304,10 @@ struct FrameArgs {
 #define GSR_SEG_WAVES 5             // resident waves per SIMD (the LDS of five blocks of 256 threads)
 #define GSR_SEG_PER_THREAD 8        // keys per thread: a block sorts 8 x threads keys at once
 #define GSR_SEG_COARSE 1024         // linear depth bins that measure a list's depth distribution
-#define GSR_SEG_CROWDED 32          // mean bin-mates of a key above which the digits are sorted instead
+// Mean bin-mates of a key above which the digits are sorted instead.  128 lists
+// of 2000 keys, whole binning: with 32 mates 50 us placed and 65 by digits, with
+// 64 58 and 66, with 128 68 and 65, with 250 91 and 66.
+#define GSR_SEG_CROWDED 64
 #define GSR_FWD_LONG 4096           // least list length of a tile composited in parts (power of 2)
 #define GSR_FWD_WAVES 5120          // resident compositing waves (256 CUs x 4 SIMDs x 5)
 #ifndef GSR_FWD_SPLIT

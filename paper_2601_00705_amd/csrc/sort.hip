@@ -68,7 +68,6 @@ struct SegLds {
         uint32_t fine[ITEMS + 1];            // fine counts, then starts
         struct {
             uint32_t wcnt[WAVES][256];       // radix sort: per-wave digit counters, then wave offsets
-            uint32_t dstart[256];            // and the block-local start of each digit
         };
     };
     uint32_t starts[GSR_SEG_COARSE + 1];     // a long list's coarse bins: counts, then starts
@@ -80,8 +79,7 @@ struct SegLds {
 // Stable ranking of the block's items by digit (key >> shift) & 255.  Item
 // (r, lane) of wave w has index w * R * 64 + r * 64 + lane; on return
 // pos[r] is its position in digit order (digit-major, index order within a
-// digit) or ~0 for an item past m, and L.dstart[] holds the first position
-// of each digit.
+// digit) or ~0 for an item past m.
 template <int WAVES, int MAXR>
 __device__ __forceinline__ void rank_items(const unsigned long long* key, int R, int m, int shift, uint32_t* pos,
                                            SegLds<WAVES>& L)
@@ -123,7 +121,6 @@ __device__ __forceinline__ void rank_items(const unsigned long long* key, int R,
     if (tid < 256) {
         uint32_t ds = incl - tot;
         for (int k = 0; k < w; ++k) ds += L.wsum[k];
-        L.dstart[tid] = ds;
         for (int k = 0; k < WAVES; ++k) {
             const uint32_t c = L.wcnt[k][tid];
             L.wcnt[k][tid] = ds;
