@@ -224,7 +224,9 @@ gsr_status gsr_bin(gsr_plan *plan, void *stream);
  * (number of blended entries per pixel) may be NULL.  n_contrib is the list
  * position + 1 of the last blended entry of the pixel's tile list; it is
  * what gsr_render_bwd replays.  rgb holds float32 values, or IEEE binary16
- * (uint16_t bit patterns, rounded to nearest) for a mixed-precision plan. */
+ * (uint16_t bit patterns, rounded to nearest) for a mixed-precision plan.  A
+ * colour that is infinite or NaN makes the pixels that blend its Gaussian so,
+ * and no others. */
 gsr_status gsr_render_fwd(gsr_plan *plan, void *rgb, float *T_final, int32_t *n_contrib, int32_t *n_blend,
                           void *stream);
 
@@ -280,7 +282,10 @@ gsr_status gsr_loss_mapping(gsr_plan *plan, const float *rgb, const float *targe
  * later changes to the poses and parameters (device memory) but not to
  * pose_only (capture again to change which views are pose-only).  grads
  * may be NULL (pose gradients only); d_xi: device [n_views][6] or NULL.
- * g and poses must be the values given to gsr_project. */
+ * g and poses must be the values given to gsr_project.  An upstream gradient
+ * that is infinite or NaN reaches the Gaussians that its pixel blends, a
+ * colour that is not finite also those blended in front of it at the same
+ * pixels, and no others (d_xi sums over all Gaussians of its view). */
 gsr_status gsr_render_bwd(gsr_plan *plan, const gsr_gaussians *g, const float *poses, const float *T_final,
                           const int32_t *n_contrib, const float *dL_drgb, const float *dL_dT,
                           const uint8_t *pose_only, gsr_grads *grads, float *d_xi, void *stream);

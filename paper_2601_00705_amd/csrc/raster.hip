@@ -53,6 +53,8 @@
 // it takes them in batches of mostly small entries (479 -> 419 us).
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace gsr {
 
 #define GSR_LOG2E 1.4426950408889634f
@@ -122,9 +124,15 @@ __device__ __forceinline__ Staged load_staged(const RasterArgs& a, uint32_t slot
     return t;
 }
 
-// Returns the entry's opacity.
+// What the batch loops ask of an entry before its batch is walked: its
+// opacity, and whether a component of its colour is infinite or NaN.
+struct Entry {
+    float o;
+    bool odd;
+};
+
 template <bool MIXED>
-__device__ __forceinline__ float stage_record(const RasterArgs& a, uint32_t slot, double xc, double yc,
+__device__ __forceinline__ Entry stage_record(const RasterArgs& a, uint32_t slot, double xc, double yc,
                                               LdsRec& r)
 {
     const Staged sr = load_staged<MIXED>(a, slot);
@@ -137,7 +145,7 @@ __device__ __forceinline__ float stage_record(const RasterArgs& a, uint32_t slot
     r.p1 = make_float4((float)(2.0 * k * sr.B), (float)(k * sr.C), sr.o, thr);
     r.p2 = make_float4(sr.r, sr.g, sr.b, __uint_as_float(slot));
     r.p3 = make_float4((float)ox, (float)oy, 1.0f / sr.o, 2.0f * r.p1.y);
-    return sr.o;
+    return {sr.o, !(__builtin_isfinite(sr.r) && __builtin_isfinite(sr.g) && __builtin_isfinite(sr.b))};
 }
 
 // writes one colour value of the image (float32, or binary16 when MIXED)
@@ -354,7 +362,7 @@ __device__ __forceinline__ void fwd_batch(const LdsRec* rec, int cnt, uint32_t p
 // the next.  T never grows, so no pixel stops within the four unless it ends
 // below T_min (or NaN); then they are taken one by one.  Records cnt .. up to
 // a multiple of four must be null (thr = +inf).
-template <int PPT, int GSR_BATCH, bool COUNT>
+template <int PPT, bool COUNT>
 __device__ __forceinline__ void fwd_batch4(const LdsRec* rec, int cnt, uint32_t pos0, float amax, float tmin,
                                            float dx, float (&dy)[PPT], float (&T)[PPT], float (&C0)[PPT],
                                            float (&C1)[PPT], float (&C2)[PPT], uint32_t (&last)[PPT],
@@ -436,6 +444,33 @@ __device__ __forceinline__ void fwd_batch4(const LdsRec* rec, int cnt, uint32_t 
     }
 }
 
+// A colour that is infinite or NaN belongs to the pixels that blend it alone,
+// but the loops add 0 times an entry's colour to the wave's other pixels, and
+// the four-at-a-time loop also that of an entry that no pixel takes.  Its odd
+// components are therefore staged as 0, a batch with such a colour is walked
+// entry by entry, and the pixels that have blended the entry (its position is
+// their last) get the components then.
+__device__ __forceinline__ void hide_odd(LdsRec& r)
+{
+    r.p2.x = __builtin_isfinite(r.p2.x) ? r.p2.x : 0.0f;
+    r.p2.y = __builtin_isfinite(r.p2.y) ? r.p2.y : 0.0f;
+    r.p2.z = __builtin_isfinite(r.p2.z) ? r.p2.z : 0.0f;
+}
+
+template <int PPT, bool MIXED>
+__device__ __forceinline__ void add_odd(const RasterArgs& a, const LdsRec& r, uint32_t pos1, const uint32_t (&last)[PPT],
+                                        float (&C0)[PPT], float (&C1)[PPT], float (&C2)[PPT])
+{
+    const Staged t = load_staged<MIXED>(a, __float_as_uint(r.p2.w));
+    const float x = t.r - r.p2.x, y = t.g - r.p2.y, z = t.b - r.p2.z;
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        C0[k] += last[k] == pos1 ? x : 0.0f;
+        C1[k] += last[k] == pos1 ? y : 0.0f;
+        C2[k] += last[k] == pos1 ? z : 0.0f;
+    }
+}
+
 // COUNT: also count the blended entries per pixel (into a.n_blend); a
 // separate instantiation, so that the plain forward carries no counters.
 // ALONE: the waves are too few to hide each other's latencies (fwd_batch4).
@@ -460,12 +495,15 @@ __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>
 #pragma unroll
         for (int k = 0; k < PPT; ++k) live |= __builtin_amdgcn_ballot_w64(dy[k] == dy[k]);
         if (live == 0) break;
-        bool may = false, small = false;
+        bool may = false, small = false, odd = false;
 #pragma unroll
         for (int r = 0; r < GSR_BATCH / 64; ++r) {
             const uint32_t j = base + lane + 64 * r;
             if (j < range.y) {
-                may |= !(stage_record<MIXED>(a, a.vals[j], c.xc, c.yc, rec[lane + 64 * r]) < amax);
+                const Entry e = stage_record<MIXED>(a, a.vals[j], c.xc, c.yc, rec[lane + 64 * r]);
+                may |= !(e.o < amax);
+                odd |= e.odd;
+                if (e.odd) hide_odd(rec[lane + 64 * r]);
                 if (!ALONE && PPT == 4 && r == 0) small = few_rows(rec[lane], 0.375f * (float)a.cfg.tile_h);
             } else if (ALONE) {
                 rec[lane + 64 * r].p0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -474,7 +512,7 @@ __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>
             }
         }
         const uint64_t few = lanes(small);
-        const bool clamps = lanes(may) != 0;
+        const bool clamps = lanes(may) != 0, odds = lanes(odd) != 0;
         __syncthreads();
         const int cnt = (int)min((uint32_t)GSR_BATCH, range.y - base);
         const uint32_t pos0 = base - range.x;
@@ -484,14 +522,23 @@ __device__ __forceinline__ void fwd_tile(const RasterArgs& a, const TileCtx<PPT>
         // rows a lane there is little to skip.  With 8 pixels per lane a
         // second copy of the loop costs registers that the waves need more
         // (96 and spills instead of 88)
-        if (ALONE) {
-            fwd_batch4<PPT, GSR_BATCH, COUNT>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
-        } else if (PPT == 4 && 2 * __popcll(few) > cnt / (GSR_BATCH / 64))
-            fwd_batch<PPT, COUNT, true, PPT == 4>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
-        else if (PPT > 4 || clamps)
-            fwd_batch<PPT, COUNT, true, false>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
-        else
-            fwd_batch<PPT, COUNT, false, false>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+        if (ALONE && !odds) {
+            fwd_batch4<PPT, COUNT>(rec, cnt, pos0, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+            __syncthreads();
+            continue;
+        }
+        const int step = odds ? 1 : cnt;
+        for (int e = 0; e < cnt; e += step) {
+            const LdsRec* at = rec + e;
+            const uint32_t p = pos0 + (uint32_t)e;
+            if (!ALONE && PPT == 4 && 2 * __popcll(few) > cnt / (GSR_BATCH / 64))
+                fwd_batch<PPT, COUNT, true, PPT == 4>(at, step, p, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+            else if (ALONE || PPT > 4 || clamps)
+                fwd_batch<PPT, COUNT, true, false>(at, step, p, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+            else
+                fwd_batch<PPT, COUNT, false, false>(at, step, p, amax, tmin, c.dx, dy, T, C0, C1, C2, last, nb);
+            if (odds) add_odd<PPT, MIXED>(a, *at, p + 1u, last, C0, C1, C2);
+        }
         __syncthreads();
     }
 #pragma unroll
@@ -757,6 +804,12 @@ struct PixelSums {
         Dy = __builtin_fmaf(dd, dy, Dy);
         Dyy = __builtin_fmaf(dd, dyy, Dyy);
     }
+    // the same with the upstream gradient left out where the weight is 0
+    __device__ __forceinline__ void add_own(float2 t, float g0, float g1, float g2, float dy, float dyy)
+    {
+        const bool own = t.y != 0.0f;
+        add(t.x, t.y, own ? g0 : 0.0f, own ? g1 : 0.0f, own ? g2 : 0.0f, dy, dyy);
+    }
 };
 
 // The lane's nine screen-space partials of an entry.  power2 partials per
@@ -832,8 +885,11 @@ __device__ __forceinline__ void bwd_reduce(const RasterArgs& a, const LdsRec& r,
 // a pixel the entry does not reach takes alpha = 0, for which rcp(1) = 1
 // exactly, so T, gsk and every partial stay unchanged without selects.
 // CLAMP: the entry may clamp at alpha_max (o >= alpha_max), where alpha has
-// no gradient (dd = 0) but still attenuates.
-template <int PPT, bool CLAMP, bool DET>
+// no gradient (dd = 0) but still attenuates.  ODD: an upstream gradient or a
+// colour of the tile is infinite or NaN; it reaches the entries that its
+// pixels blend (0 times it would reach the others as well), so the pixels
+// that the entry does not reach are left out by selects.
+template <int PPT, bool CLAMP, bool DET, bool ODD>
 __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, const ColTerms& ct,
                                           const float (&p2)[PPT], const uint64_t (&on)[PPT], float amax,
                                           const TileCtx<PPT>& c, const float (&g0)[PPT], const float (&g1)[PPT],
@@ -848,14 +904,19 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
         const float alpha = in(on[k]) ? (CLAMP ? fminf(a_raw, amax) : a_raw) : 0.0f;
         const float rcp = __builtin_amdgcn_rcpf(1.0f - alpha);
         const float Tb = T[k] * rcp;
-        const float gcol = __builtin_fmaf(g0[k], r.p2.x, __builtin_fmaf(g1[k], r.p2.y, g2[k] * r.p2.z));
+        float gcol = __builtin_fmaf(g0[k], r.p2.x, __builtin_fmaf(g1[k], r.p2.y, g2[k] * r.p2.z));
+        if (ODD) gcol = in(on[k]) ? gcol : 0.0f;
         const float wgt = alpha * Tb;
         const float gsk_new = __builtin_fmaf(wgt, gcol, gsk[k]);
         float dd = __builtin_fmaf(-gsk[k], rcp, gsk_new);
         if (CLAMP) dd = a_raw < amax ? dd : 0.0f;
+        if (ODD) dd = in(on[k]) ? dd : 0.0f;
         gsk[k] = gsk_new;
         T[k] = Tb;
-        p.add(dd, wgt, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+        if (ODD)
+            p.add(dd, wgt, in(on[k]) ? g0[k] : 0.0f, in(on[k]) ? g1[k] : 0.0f, in(on[k]) ? g2[k] : 0.0f, c.dy[k], dy2[k]);
+        else
+            p.add(dd, wgt, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
     }
     bwd_reduce<DET>(a, r, ct, c.dx, p, lane, pend);
 }
@@ -863,8 +924,9 @@ __device__ __forceinline__ void bwd_entry(const RasterArgs& a, const LdsRec& r, 
 // The staged entries rec[0, cnt), from the list's position top down.
 // CLAMPS: the batch holds an entry that may clamp, so every entry is asked
 // (alpha = o G <= o: a test uniform over the wave); FULL: every pixel of the
-// tile blended an entry at top or behind it, so no position is tested.
-template <int PPT, bool CLAMPS, bool FULL, bool DET>
+// tile blended an entry at top or behind it, so no position is tested; ODD as
+// for bwd_entry.
+template <int PPT, bool CLAMPS, bool FULL, bool DET, bool ODD>
 __device__ __forceinline__ void bwd_batch(const RasterArgs& a, const LdsRec* rec, int cnt, uint32_t top, float amax,
                                           const TileCtx<PPT>& c, const uint32_t (&my_n)[PPT], const float (&g0)[PPT],
                                           const float (&g1)[PPT], const float (&g2)[PPT], const float (&dy2)[PPT],
@@ -885,9 +947,9 @@ __device__ __forceinline__ void bwd_batch(const RasterArgs& a, const LdsRec* rec
         }
         if (any == 0) continue;
         if (CLAMPS && may_clamp(r.p1.z, amax))
-            bwd_entry<PPT, true, DET>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
+            bwd_entry<PPT, true, DET, ODD>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
         else
-            bwd_entry<PPT, false, DET>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
+            bwd_entry<PPT, false, DET, ODD>(a, r, ct, p2, on, amax, c, g0, g1, g2, dy2, T, gsk, lane, pend);
     }
 }
 
@@ -935,6 +997,12 @@ __global__ __launch_bounds__(64, PPT <= 4 ? 5 : 3) void k_raster_bwd(RasterArgs 
         lane_max = max(lane_max, (uint32_t)__shfl_xor((int)lane_max, off, 64));
         lane_min = min(lane_min, (uint32_t)__shfl_xor((int)lane_min, off, 64));
     }
+    bool upstream = false;
+#pragma unroll
+    for (int k = 0; k < PPT; ++k)
+        upstream |= !(__builtin_isfinite(g0[k]) && __builtin_isfinite(g1[k]) && __builtin_isfinite(g2[k]) &&
+                      __builtin_isfinite(gsk[k]));
+    bool odd = lanes(upstream) != 0;
     // positions below this are blended by every pixel (0 where the tile
     // reaches outside the view)
     const uint32_t full = (uint32_t)uniform((int)lane_min);
@@ -944,21 +1012,28 @@ __global__ __launch_bounds__(64, PPT <= 4 ? 5 : 3) void k_raster_bwd(RasterArgs 
     for (uint32_t hi_ = end; hi_ > range.x;) {
         const uint32_t lo_ = hi_ - range.x > (uint32_t)GSR_BATCH ? hi_ - GSR_BATCH : range.x;
         const int cnt = (int)(hi_ - lo_);
-        bool may = false;
+        bool may = false, colour = false;
 #pragma unroll
         for (int r = 0; r < GSR_BATCH / 64; ++r) {
             const int t = lane + 64 * r;
-            if (t < cnt) may |= !(stage_record<MIXED>(a, a.vals[hi_ - 1 - t], c.xc, c.yc, rec[t]) < amax);
+            if (t < cnt) {
+                const Entry e = stage_record<MIXED>(a, a.vals[hi_ - 1 - t], c.xc, c.yc, rec[t]);
+                may |= !(e.o < amax);
+                colour |= e.odd;
+            }
         }
         const bool clamps = lanes(may) != 0;
+        odd |= lanes(colour) != 0;  // (and the entries before it, through gsk)
         __syncthreads();
         const uint32_t top = hi_ - 1 - range.x;
-        if (clamps)
-            bwd_batch<PPT, true, false, DET>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
+        if (odd)
+            bwd_batch<PPT, true, false, DET, true>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
+        else if (clamps)
+            bwd_batch<PPT, true, false, DET, false>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
         else if (top < full)
-            bwd_batch<PPT, false, true, DET>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
+            bwd_batch<PPT, false, true, DET, false>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
         else
-            bwd_batch<PPT, false, false, DET>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
+            bwd_batch<PPT, false, false, DET, false>(a, rec, cnt, top, amax, c, my_n, g0, g1, g2, dy2, T, gsk, lane, pend);
         __syncthreads();
         hi_ = lo_;
     }
@@ -992,13 +1067,14 @@ struct BwdFew {
 };
 
 template <int PPT, bool DET, bool MIXED>
-__global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(RasterArgs a)
+__global__ __launch_bounds__(128 * BwdFew<PPT>::waves, 4) void k_raster_bwd_few(RasterArgs a)
 {
     constexpr int W = BwdFew<PPT>::waves, Q = BwdFew<PPT>::ppt, G = GSR_BWD_GROUP, U = 4, B = 64;
     static_assert(G % U == 0 && B % G == 0 && B / G >= 4 && W <= 4 && G % (2 * W) == 0, "");
     __shared__ LdsRec rec[2][B];
     __shared__ float2 term[2][G][PPT][64];
     __shared__ uint32_t reached[2][4];  // entries that reach wave w's pixels, a bit each
+    __shared__ uint32_t rec_odd[2];     // whether a colour of rec[.] is infinite or NaN
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
     const bool replays = wave < W;
     const int w = replays ? wave : wave - W;
@@ -1021,12 +1097,15 @@ __global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(Ras
     // records i .. i + B - 1 of the replay, null past its end
     auto stage = [&](int i) {
         LdsRec& r = rec[(i / B) & 1][lane];
+        bool odd = false;
         if (i + lane < count) {
-            stage_record<MIXED>(a, a.vals[range.x + (uint32_t)(count - 1 - i - lane)], c.xc, c.yc, r);
+            odd = stage_record<MIXED>(a, a.vals[range.x + (uint32_t)(count - 1 - i - lane)], c.xc, c.yc, r).odd;
         } else {
             r.p0 = r.p2 = r.p3 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             r.p1 = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
         }
+        const uint64_t any = lanes(odd);
+        if (lane == 0) rec_odd[(i / B) & 1] = any != 0;
     };
     if (wave == W) stage(0);
 
@@ -1035,6 +1114,7 @@ __global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(Ras
         const TileCtx<Q> o = tile_ctx_at<Q>(a, tile, w * Q);
         float T[Q], gsk[Q], h0[Q], h1[Q], h2[Q];
         uint32_t my_n[Q];
+        bool upstream = false;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             float Tf = 1.0f, gT = 0.0f;
@@ -1050,9 +1130,14 @@ __global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(Ras
             }
             T[q] = Tf;
             gsk[q] = __builtin_fmaf(gT, Tf, Tf * (h0[q] * a.cfg.bg0 + h1[q] * a.cfg.bg1 + h2[q] * a.cfg.bg2));
+            upstream |= !(__builtin_isfinite(h0[q]) && __builtin_isfinite(h1[q]) && __builtin_isfinite(h2[q]) &&
+                          __builtin_isfinite(gsk[q]));
         }
+        bool odd = lanes(upstream) != 0;
         __syncthreads();
-        for (int gr = 0; gr < groups; ++gr) {
+        // group gr; ODD as for bwd_entry
+        auto replay = [&](auto odd_variant, int gr) {
+            constexpr bool ODD = decltype(odd_variant)::value;
             const LdsRec* rg = &rec[(gr * G / B) & 1][gr * G % B];
             const int buf = gr & 1;
             const uint32_t top = (uint32_t)(count - 1 - gr * G);  // (below 0 only at null records)
@@ -1087,7 +1172,8 @@ __global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(Ras
                         alpha[u][q] = in(on[u][q]) ? fminf(p2[u][q], lim) : 0.0f;
                         rcp[u][q] = __builtin_amdgcn_rcpf(1.0f - alpha[u][q]);
                         gcol[u][q] = __builtin_fmaf(h0[q], r[u].p2.x, __builtin_fmaf(h1[q], r[u].p2.y, h2[q] * r[u].p2.z));
-                        on[u][q] = lanes(p2[u][q] < lim);
+                        if (ODD) gcol[u][q] = in(on[u][q]) ? gcol[u][q] : 0.0f;
+                        on[u][q] = (ODD ? on[u][q] : ~0ull) & lanes(p2[u][q] < lim);
                     }
                 }
 #pragma unroll
@@ -1105,10 +1191,23 @@ __global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(Ras
                 }
             }
             if (lane == 0) reached[buf][w] = reach;
+        };
+        // (an odd colour stays in gsk: two loops, so that the first keeps the
+        // registers and the schedule that it has without the second)
+        int gr = 0;
+        for (; gr < groups; ++gr) {
+            if (gr * G % B == 0) odd |= uniform((int)rec_odd[(gr * G / B) & 1]) != 0;
+            if (odd) break;
+            replay(std::false_type{}, gr);
+            __syncthreads();
+        }
+        for (; gr < groups; ++gr) {
+            replay(std::true_type{}, gr);
             __syncthreads();
         }
     } else {
         float g0[PPT], g1[PPT], g2[PPT], dy2[PPT];
+        bool upstream = false;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             g0[k] = g1[k] = g2[k] = 0.0f;
@@ -1118,7 +1217,9 @@ __global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(Ras
                 g2[k] = a.dL_drgb[c.rgb0(k) + 2 * c.plane];
             }
             dy2[k] = c.dy[k] * c.dy[k];
+            upstream |= !(__builtin_isfinite(g0[k]) && __builtin_isfinite(g1[k]) && __builtin_isfinite(g2[k]));
         }
+        const bool odd = lanes(upstream) != 0;
         PendingField pend{0, 0, 0.0f};
         __syncthreads();
         // step gr reduces group gr - 1 (after the last barrier, the last)
@@ -1148,10 +1249,18 @@ __global__ __launch_bounds__(128 * BwdFew<PPT>::waves) void k_raster_bwd_few(Ras
                         t1[k] = term[buf][e1][k][lane];
                     }
                     PixelSums p0, p1;
+                    if (odd) {  // (a pixel that the entry does not reach has weight 0)
 #pragma unroll
-                    for (int k = 0; k < PPT; ++k) {
-                        if ((hit[k / Q] >> e0) & 1u) p0.add(t0[k].x, t0[k].y, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
-                        if ((hit[k / Q] >> e1) & 1u) p1.add(t1[k].x, t1[k].y, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+                        for (int k = 0; k < PPT; ++k) {
+                            if ((hit[k / Q] >> e0) & 1u) p0.add_own(t0[k], g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+                            if ((hit[k / Q] >> e1) & 1u) p1.add_own(t1[k], g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < PPT; ++k) {
+                            if ((hit[k / Q] >> e0) & 1u) p0.add(t0[k].x, t0[k].y, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+                            if ((hit[k / Q] >> e1) & 1u) p1.add(t1[k].x, t1[k].y, g0[k], g1[k], g2[k], c.dy[k], dy2[k]);
+                        }
                     }
                     if (has0 && has1) {
                         float v0[9], v1[9];
