@@ -352,7 +352,8 @@ gsr_status gsr_seed_triangulate(int64_t n, int32_t n_neighbours, const gsr_seed_
 /* Isotropic initial scale of the valid seeds: log_scale [3][n] (device) =
  * log(max(d, floor_scale)) on every axis, d the mean distance to the 3
  * nearest other valid seeds (all of them when fewer exist; floor_scale when
- * none); 0 for invalid seeds.  mean [3][n], valid [n] as written by
+ * none); 0 for invalid seeds.  A seed with a coordinate that is not finite is
+ * no neighbour and takes floor_scale.  mean [3][n], valid [n] as written by
  * gsr_seed_triangulate.  workspace: caller-owned device memory of
  * gsr_seed_scale_workspace_bytes(n) bytes (0 for n out of range), reused
  * freely between calls; calls that share it must be ordered. */
@@ -394,7 +395,8 @@ gsr_status gsr_seed_frame(int64_t n, const float *mean, const int32_t *valid, co
  * merging of Sec. "Insertion, Lightweight Merging, and Pruning".  mean
  * [3][n], valid [n] (device; 0 excludes a Gaussian both as a query and as a
  * neighbour).  Output nn_index [n] (device): the neighbour's index, -1 for
- * an invalid Gaussian or one with no valid other.  workspace: device,
+ * an invalid Gaussian or one with no valid other (a Gaussian with a
+ * coordinate that is not finite has no neighbour and is none).  workspace: device,
  * gsr_seed_scale_workspace_bytes(n) bytes (the same search).  n out of
  * [0, 2^31) or a null buffer: GSR_EINVAL, nothing enqueued. */
 gsr_status gsr_nearest(int64_t n, const float *mean, const int32_t *valid, void *workspace, size_t workspace_bytes,

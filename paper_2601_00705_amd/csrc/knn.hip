@@ -96,6 +96,13 @@ __global__ __launch_bounds__(KNN_THREADS) void k_knn_box(KnnArgs a)
     }
 }
 
+// a point that is not finite has no neighbours (and is none: its distances
+// are infinite or NaN)
+__device__ __forceinline__ bool finite_point(const float4& p)
+{
+    return __builtin_isfinite(p.x) && __builtin_isfinite(p.y) && __builtin_isfinite(p.z);
+}
+
 // bit k of the 21-bit x moved to bit 3 k
 __device__ __forceinline__ uint64_t spread21(uint64_t x)
 {
@@ -366,7 +373,8 @@ __global__ __launch_bounds__(512) void k_knn_sort(KnnArgs a)
             const uint32_t at = start + c0 + (uint32_t)k;
             a.pts[at] = p;
             // the boxes of the leaf's 8 groups, then its own; a point that
-            // is NaN is in none
+            // is not finite is in none
+            if (!finite_point(p)) p.x = p.y = p.z = NAN;
             const float q[3] = {p.x, p.y, p.z};
             const uint32_t leaf = at >> 6;
             float* g = a.groups + 48 * (int64_t)leaf;
@@ -446,8 +454,9 @@ __device__ __forceinline__ bool knn_before(double d, uint32_t j, double bd, uint
     return d < bd || (d == bd && j < bj);
 }
 
-// A lane's query: its K nearest so far, ascending.  bound is negative for a
-// lane without a query.
+// A lane's query: its K nearest so far, ascending (an entry at distance
+// infinity is none, and no candidate at distance infinity or NaN enters).
+// bound is negative for a lane without a query.
 template <int K>
 struct Nearest {
     float px, py, pz, bound;
@@ -465,7 +474,7 @@ struct Nearest {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             d[k] = INFINITY;
-            j[k] = KNN_NONE;
+            j[k] = 0u;
         }
     }
     __device__ __forceinline__ void insert(double x, uint32_t i)
@@ -683,7 +692,7 @@ __device__ __forceinline__ void search(Q& q, const KnnArgs& a, int leaf, int lea
 
 __device__ __forceinline__ bool is_query(const float4& p)
 {
-    return __float_as_uint(p.w) != KNN_NONE && p.x == p.x && p.y == p.y && p.z == p.z;
+    return __float_as_uint(p.w) != KNN_NONE && finite_point(p);
 }
 
 // the query's outputs: its log-scale (when asked for) and its nearest
@@ -696,7 +705,7 @@ __device__ __forceinline__ void knn_write(const KnnArgs& a, int64_t i, const Nea
         int found = 0;
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            if (q.j[k] != KNN_NONE) {
+            if (q.d[k] < INFINITY) {
                 sum += sqrt(q.d[k]);
                 ++found;
             }
@@ -705,7 +714,7 @@ __device__ __forceinline__ void knn_write(const KnnArgs& a, int64_t i, const Nea
 #pragma unroll
         for (int c = 0; c < 3; ++c) a.log_scale[(int64_t)c * a.n + i] = ls;
     }
-    if (a.nn_index) a.nn_index[i] = (int32_t)q.j[0];  // KNN_NONE is -1
+    if (a.nn_index) a.nn_index[i] = q.d[0] < INFINITY ? (int32_t)q.j[0] : -1;
 }
 
 template <int K>
