@@ -1166,10 +1166,14 @@ extern "C" gsr_status gsr_compact(int64_t n, int32_t rows, const float* src, con
 // ---- spatial storage order -------------------------------------------------
 
 // workspace carve-up of gsr_spatial_order: code[2], val[2], hist, box
-// partials, digit totals, each on a 256-byte boundary
+// partials, digit totals, each on a 256-byte boundary.  The size grows with n,
+// so that a workspace for a map's capacity serves any smaller map: past
+// GSR_RADIX_SMALL keys, where the tiles get larger and the blocks fewer, the
+// block counts keep the room that GSR_RADIX_SMALL keys take.
 static size_t order_layout(int64_t n, size_t off[7])
 {
-    const int64_t blocks = (n + radix_tile(n) - 1) / radix_tile(n);
+    const int64_t small = std::min<int64_t>(n, GSR_RADIX_SMALL);
+    const int64_t blocks = std::max((n + radix_tile(n) - 1) / radix_tile(n), (small + radix_tile(small) - 1) / radix_tile(small));
     size_t at = 0;
     auto take = [&](size_t bytes) {
         const size_t o = at;
