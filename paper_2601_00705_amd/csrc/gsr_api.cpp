@@ -858,7 +858,8 @@ KnnLayout knn_layout(int64_t n)
     L.placed = take(sizeof(float4) * slots);
     L.pts = take(sizeof(float4) * slots);
     L.mom = take(sizeof(double) * 10 * slots);
-    L.total = o;
+    // the direct search keeps nothing in memory
+    L.total = n <= GSR_KNN_SMALL ? 256 : o;
     return L;
 }
 }  // namespace

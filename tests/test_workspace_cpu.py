@@ -31,3 +31,11 @@ def test_order_takes_its_capacity_workspace():
         # the index lies inside the workspace: refused, but for that
         assert raw.gsr_spatial_order(n, ctypes.c_void_p(1 << 30), 64, ws, ws, have, None) == lib.EINVAL
         assert b"overlap" in raw.gsr_last_error(), n
+
+
+def test_direct_search_needs_no_workspace():
+    """Up to 16,384 points the searches keep nothing in memory."""
+    raw = lib.raw()
+    for n in (1, 1000, 16384):
+        assert 0 < raw.gsr_seed_scale_workspace_bytes(n) <= 256
+    assert raw.gsr_seed_scale_workspace_bytes(16385) > 256
