@@ -1048,14 +1048,16 @@ extern "C" size_t gsr_prune_workspace_bytes(int64_t n)
 }
 
 // the pruning scan over a given block-count buffer (the caller's workspace
-// or the no-allocation scratch); arguments already hold n in range
+// or the no-allocation scratch) of one count per chunk; arguments already
+// hold n in range
 static gsr_status prune_run(int64_t n, const int32_t* m_obs, const float* v_vis, const float* log_scale,
                             const float* opacity_logit, const gsr_prune_config* cfg, int32_t* keep_index,
-                            int64_t* kept, uint32_t* block_count, void* stream, const char* where)
+                            int64_t* kept, uint32_t* block_count, int32_t chunk, void* stream, const char* where)
 {
     PruneArgs a{};
     a.n = n;
-    a.blocks = (int32_t)((n + GSR_PRUNE_CHUNK - 1) / GSR_PRUNE_CHUNK);
+    a.chunk = chunk;
+    a.blocks = (int32_t)((n + chunk - 1) / chunk);
     a.m_obs = m_obs;
     a.v_vis = v_vis;
     a.log_scale = log_scale;
@@ -1092,7 +1094,7 @@ extern "C" gsr_status gsr_prune(int64_t n, const int32_t* m_obs, const float* v_
     if (st != GSR_OK) return st;
     if (!workspace) return fail(GSR_EINVAL, "null argument");
     return prune_run(n, m_obs, v_vis, log_scale, opacity_logit, cfg, keep_index, kept, (uint32_t*)workspace,
-                     stream, "gsr_prune");
+                     GSR_PRUNE_CHUNK, stream, "gsr_prune");
 }
 
 // ---- pruning without allocation --------------------------------------------
@@ -1103,8 +1105,11 @@ extern "C" gsr_status gsr_prune(int64_t n, const int32_t* m_obs, const float* v_
 // device is taken once, with that device current, by hipGetSymbolAddress,
 // and used from then on.  Every call on one GPU shares the array: calls that
 // overlap on one GPU (two streams, two threads) race.  The scan writes every
-// count it later reads, so nothing needs clearing between calls.
-static __device__ __align__(256) uint32_t scratch[(GSR_PRUNE_NOALLOC_MAX_N + GSR_PRUNE_CHUNK - 1) / GSR_PRUNE_CHUNK + 1];
+// count it later reads, so nothing needs clearing between calls.  Its 65,536
+// counts are one per GSR_PRUNE_CHUNK Gaussians up to 2^25 of them, and one per
+// GSR_PRUNE_CHUNK_MOST above.
+static __device__ __align__(256) uint32_t scratch[GSR_PRUNE_NOALLOC_MAX_N / GSR_PRUNE_CHUNK_MOST];
+static_assert(sizeof(scratch) == 256 * 1024, "the size that gsr.h states");
 
 static std::mutex g_scratch_mu;
 static void* g_scratch_ptr[GSR_MAX_DEVICES];
@@ -1140,7 +1145,9 @@ extern "C" gsr_status gsr_prune_noalloc(int64_t n, const int32_t* m_obs, const f
     uint32_t* block_count = nullptr;
     st = scratch_address(&block_count);
     if (st != GSR_OK) return st;
-    return prune_run(n, m_obs, v_vis, log_scale, opacity_logit, cfg, keep_index, kept, block_count, stream,
+    const int64_t counts = (int64_t)(sizeof(scratch) / sizeof(scratch[0]));
+    const int32_t chunk = n <= counts * GSR_PRUNE_CHUNK ? GSR_PRUNE_CHUNK : GSR_PRUNE_CHUNK_MOST;
+    return prune_run(n, m_obs, v_vis, log_scale, opacity_logit, cfg, keep_index, kept, block_count, chunk, stream,
                      "gsr_prune_noalloc");
 }
 
@@ -1304,6 +1311,7 @@ extern "C" gsr_status gsr_keep_list(int64_t n, const int32_t* mask, int32_t* kee
     if (n <= 0 || n > (1ll << 31) - 1) return fail(GSR_EINVAL, "n must lie in [1, 2^31)");
     PruneArgs a{};
     a.n = n;
+    a.chunk = GSR_PRUNE_CHUNK;
     a.blocks = (int32_t)((n + GSR_PRUNE_CHUNK - 1) / GSR_PRUNE_CHUNK);
     a.mask = mask;
     a.block_count = (uint32_t*)workspace;

@@ -145,6 +145,7 @@ struct MapLossArgs {
 
 #define GSR_ADAM_BLOCKS 1024         // blocks of the gradient-norm pass
 #define GSR_PRUNE_CHUNK 512          // Gaussians per block of the pruning scan (2048: 7 us a pass at 30k for 4)
+#define GSR_PRUNE_CHUNK_MOST 2048    // the same where the fixed scratch would not hold the blocks' counts
 
 struct AdamArgs {
     float* p[5];               // planes: mean, quat, log_scale, opacity_logit, colour
@@ -173,7 +174,8 @@ struct CovisArgs {
 
 struct PruneArgs {
     int64_t n;
-    int32_t blocks;            // ceil(n / GSR_PRUNE_CHUNK)
+    int32_t chunk;             // Gaussians per block, a multiple of 256
+    int32_t blocks;            // ceil(n / chunk)
     const int32_t* m_obs;
     const float* v_vis;
     const float* log_scale;    // [3][n]

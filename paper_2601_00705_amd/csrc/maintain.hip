@@ -241,13 +241,13 @@ __device__ __forceinline__ bool prune_keep(const PruneArgs& a, int64_t i)
     return !drop;
 }
 
-// per block of GSR_PRUNE_CHUNK Gaussians: the number kept
+// per block of a.chunk Gaussians: the number kept
 __global__ __launch_bounds__(256) void k_prune_count(PruneArgs a)
 {
     __shared__ uint32_t red[4];
-    const int64_t base = (int64_t)blockIdx.x * GSR_PRUNE_CHUNK;
+    const int64_t base = (int64_t)blockIdx.x * a.chunk;
     uint32_t c = 0;
-    for (int j = threadIdx.x; j < GSR_PRUNE_CHUNK; j += 256) {
+    for (int j = threadIdx.x; j < a.chunk; j += 256) {
         const int64_t i = base + j;
         if (i < a.n && prune_keep(a, i)) ++c;
     }
@@ -289,10 +289,10 @@ __global__ __launch_bounds__(1024) void k_prune_scan(PruneArgs a)
 __global__ __launch_bounds__(256) void k_prune_emit(PruneArgs a)
 {
     __shared__ uint32_t wsum[4];
-    const int64_t base = (int64_t)blockIdx.x * GSR_PRUNE_CHUNK;
+    const int64_t base = (int64_t)blockIdx.x * a.chunk;
     uint32_t run = a.block_count[blockIdx.x];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int j0 = 0; j0 < GSR_PRUNE_CHUNK; j0 += 256) {
+    for (int j0 = 0; j0 < a.chunk; j0 += 256) {
         const int64_t i = base + j0 + threadIdx.x;
         const bool keep = i < a.n && prune_keep(a, i);
         const unsigned long long bal = __ballot(keep);
