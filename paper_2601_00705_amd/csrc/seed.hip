@@ -18,6 +18,7 @@
 //   kept point's projection).
 // The neighbour searches behind the initial scales are in knn.hip.
 #include "kernels.h"
+#include "seed_lanes.h"
 
 namespace gsr {
 
@@ -157,7 +158,7 @@ __device__ __forceinline__ Hypothesis hypothesis(const SeedArgs& a, int64_t i, i
     return hy;
 }
 
-// G lanes to a pixel (4 from three neighbours on): each solves the systems of
+// G lanes to a pixel (seed_lanes): each solves the systems of
 // every G-th neighbour, the hypotheses are compared in the neighbours' order,
 // and the supporting views and the colour's channels are dealt to the lanes.
 // Bound by the FP64 rotations where pixels fill the chip (500k, four
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(GSR_SEED_THREADS) void k_seed_triangulate(SeedArgs 
 hipError_t launch_seed_triangulate(const SeedArgs& a, hipStream_t s)
 {
     if (a.n == 0) return hipSuccess;
-    const int G = a.K >= 3 ? 4 : (a.K == 2 ? 2 : 1);
+    const int G = seed_lanes(a.n, a.K);
     const int64_t blocks = (a.n * G + GSR_SEED_THREADS - 1) / GSR_SEED_THREADS;
     const dim3 grid((unsigned)blocks), block(GSR_SEED_THREADS);
     if (G == 4) hipLaunchKernelGGL(k_seed_triangulate<4>, grid, block, 0, s, a);
