@@ -40,3 +40,39 @@ def test_infinite_points(n, finite):
     assert np.array_equal(nn[q], q[d.argmin(0)])
     want = np.log(np.maximum(np.sort(d, 0)[:min(3, len(q) - 1)].mean(0), FLOOR))
     assert np.all(np.abs(ls[:, q] - want) <= 1e-6 * np.maximum(1.0, np.abs(want)))
+
+
+@pytest.mark.parametrize("n,period,phase", [(1 << 20, 2, 0), (1 << 20, 256, 0), (1 << 17, 2, 1), (40960, 40, 0),
+                                            (1 << 22, 256, 0)])
+def test_periodic_validity(n, period, phase):
+    """Valid points that follow the storage order (every other pixel, all but
+    one column): the search is exact, and takes no longer than it does with
+    as many valid points in any order.  Valid points that the samples miss
+    all land in one bucket and cost tens of times that, so the bound is 5."""
+    print(f"[knn] {n} points, all but every {period}th", flush=True)
+    rng = np.random.default_rng(period)
+    X = torch.from_numpy(rng.uniform(-1, 1, (3, n)).astype(np.float32)).cuda()
+    valid = (np.arange(n) % period != phase).astype(np.int32)
+    V, W = torch.from_numpy(valid).cuda(), torch.from_numpy(rng.permutation(valid)).cuda()
+    out = {}
+    for key, v in (("order", V), ("shuffled", W)):
+        times = []
+        for _ in range(4):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            nn = maintain.nearest(X, v)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        out[key] = min(times)
+        if key == "order":
+            got = nn.cpu().numpy()
+    print(f"[knn] {out['order']:.3f} ms, shuffled {out['shuffled']:.3f} ms", flush=True)
+    assert out["order"] <= 5 * out["shuffled"]
+    assert np.all(got[valid == 0] == -1)
+    Xd, ok = X.double(), V != 0
+    for i in rng.choice(np.nonzero(valid)[0], 40, replace=False):
+        d = ((Xd - Xd[:, i:i + 1]) ** 2).sum(0)
+        d[~ok] = np.inf
+        d[i] = np.inf
+        assert int(d.argmin()) == got[i]
