@@ -842,7 +842,7 @@ KnnLayout knn_layout(int64_t n)
         o = align256(o + (bytes ? bytes : 1));
         return at;
     };
-    L.box = take(sizeof(float) * 8 * GSR_KNN_BLOCKS);
+    L.box = take(sizeof(float) * GSR_KNN_BOX * GSR_KNN_BLOCKS);
     L.tree = take(sizeof(KnnTree));
     L.split = take(sizeof(uint64_t) * nb);
     L.total_b = take(sizeof(uint32_t) * nb);

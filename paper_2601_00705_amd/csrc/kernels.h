@@ -210,6 +210,7 @@ struct CompactArgs {
 
 #define GSR_SEED_MAX_NEIGHBOURS 8
 #define GSR_KNN_BLOCKS 256          // blocks of the points' bounding-box pass
+#define GSR_KNN_BOX 9               // floats of one block: box (lo, hi), a point
 #define GSR_KNN_SMALL 16384         // up to this many points are searched without a tree
 
 struct SeedView {
@@ -238,10 +239,14 @@ struct SeedArgs {
     float* kappa_bar;          // [n]
 };
 
-// the points' Morton cells, and how many leaves of 64 points they make
+// the cells along whose Hilbert curve the points are sorted (knn_cell), and how
+// many leaves of 64 points they make
 struct KnnTree {
-    double lo[3];              // least coordinates of the finite valid points
-    double scale;              // cells per unit length
+    double centre[3];
+    double inv_half;           // 1 / half the side of the cube about the bulk of the points
+    double knee;               // scaled offset above which its logarithm is taken
+    double least[3];           // least warped offset of a finite valid point, per axis
+    double cells;              // cells per unit of it
     int32_t leaves;
 };
 
@@ -253,7 +258,7 @@ struct KnnArgs {
     int32_t buckets;           // buckets of the sample sort: 256, 1024 or 4096
     int32_t per_block;         // points per block of the counting passes
     int64_t max_leaves;
-    float* box;                // [GSR_KNN_BLOCKS][8] partial boxes
+    float* box;                // [GSR_KNN_BLOCKS][GSR_KNN_BOX]
     KnnTree* tree;
     uint64_t* split;           // [buckets] least code of each bucket
     uint32_t* total;           // [buckets] points

@@ -11,9 +11,10 @@
 // own leaf gives each query a first bound, then the leaves whose box lies
 // within some query's bound are scanned from LDS.
 //
-//   k_knn_box      partial boxes of the finite valid points
-//   k_knn_split    sample sort's splitters: every fourth of 4 samples per
-//                  bucket, ranked by counting (each block ranks 64 samples)
+//   k_knn_box      partial boxes of the finite valid points, and some of them
+//   k_knn_split    the cells, and sample sort's splitters: every fourth of 4
+//                  samples per bucket, ranked by counting (each block ranks
+//                  64 samples)
 //   k_knn_count    each point's bucket, and per block and bucket its offset
 //                  inside the bucket (one atomic per block and bucket)
 //   k_knn_place    points into their buckets (starts at multiples of 64)
@@ -43,6 +44,8 @@ namespace gsr {
 
 #define KNN_THREADS 256
 #define KNN_NONE 0xffffffffu
+#define KNN_FAR 1024.0 // extent of the points, in half the width of their bulk, above which the cells are warped
+#define GSR_KNN_LN2 0.69314718f
 #define KNN_REFINE 20  // length of a wave's list of boxes above which it is cut down query by query
 
 // ---------------------------------------------------------------------------
@@ -60,8 +63,31 @@ __device__ __forceinline__ float wave_maxf(float x)
     return x;
 }
 
-// partial box of the finite valid points of a block's stride, and the bucket
-// counters cleared
+// a point that is not finite has no neighbours (and is none: its distances
+// are infinite or NaN)
+__device__ __forceinline__ bool finite_point(const float4& p)
+{
+    return __builtin_isfinite(p.x) && __builtin_isfinite(p.y) && __builtin_isfinite(p.z);
+}
+
+// Sample s of S: a point of the s-th of S equal runs of points, at a place in
+// the run that looks random.  (The first point of every run lets a validity
+// that follows the storage order, every other pixel of a row of 1024 say, hide
+// all valid points from the samples: 2^20 points went into one bucket, and the
+// nearest search took 18 ms instead of 0.5.)
+__device__ __forceinline__ int64_t sample_point(int s, int S, int64_t n)
+{
+    uint32_t h = (uint32_t)s + 1u;
+    h = (h ^ (h >> 16)) * 0x7feb352du;
+    h = (h ^ (h >> 15)) * 0x846ca68bu;
+    h ^= h >> 16;
+    const int64_t i0 = (int64_t)s * n / S, len = (int64_t)(s + 1) * n / S - i0;
+    return i0 + (int64_t)(((uint64_t)h * (uint64_t)len) >> 32);
+}
+
+// Partial box of the finite valid points of a block's stride, one such point
+// of the block's run (NaN if 64 samples show none), and the bucket counters
+// cleared.
 __global__ __launch_bounds__(KNN_THREADS) void k_knn_box(KnnArgs a)
 {
     __shared__ float red[6][KNN_THREADS / 64];
@@ -92,15 +118,19 @@ __global__ __launch_bounds__(KNN_THREADS) void k_knn_box(KnnArgs a)
         const int k = threadIdx.x;
         float r = red[k][0];
         for (int j = 1; j < KNN_THREADS / 64; ++j) r = k < 3 ? fminf(r, red[k][j]) : fmaxf(r, red[k][j]);
-        a.box[blockIdx.x * 8 + k] = r;
+        a.box[blockIdx.x * GSR_KNN_BOX + k] = r;
     }
-}
-
-// a point that is not finite has no neighbours (and is none: its distances
-// are infinite or NaN)
-__device__ __forceinline__ bool finite_point(const float4& p)
-{
-    return __builtin_isfinite(p.x) && __builtin_isfinite(p.y) && __builtin_isfinite(p.z);
+    if (w == 3) {
+        const int64_t i = sample_point(blockIdx.x * 64 + lane, GSR_KNN_BLOCKS * 64, a.n);
+        float4 p = make_float4(a.mean[i], a.mean[a.n + i], a.mean[2 * a.n + i], 0.0f);
+        if (!a.valid[i] || !finite_point(p)) p.x = NAN;
+        const uint64_t have = __ballot(p.x == p.x);
+        if (lane == (have ? __ffsll((unsigned long long)have) - 1 : 0)) {
+            a.box[blockIdx.x * GSR_KNN_BOX + 6] = p.x;
+            a.box[blockIdx.x * GSR_KNN_BOX + 7] = p.y;
+            a.box[blockIdx.x * GSR_KNN_BOX + 8] = p.z;
+        }
+    }
 }
 
 // bit k of the 21-bit x moved to bit 3 k
@@ -115,20 +145,37 @@ __device__ __forceinline__ uint64_t spread21(uint64_t x)
     return x;
 }
 
-// Place along the Hilbert curve through the 2^63 cubic cells of the points'
-// box, 2^21 to its longest side (Skilling 2004, transposed axes); consecutive
-// cells share a face, where Morton order jumps and leaves a share of the
-// boxes large.  Non-finite points come last.
+// Cell of coordinate x along axis c, below 2^21.  The cells are equal parts of
+// the points' box, unless that is more than KNN_FAR times as wide as the cube
+// that holds the bulk of the points: then the offsets from the cube's centre
+// are taken as they are inside it and grow with their logarithm outside, so
+// that no outlier makes the bulk's cells coarse.  With cells of the whole box,
+// one point 10^8 scene sizes away put all others in a few cells, and the
+// radius search through leaves of points in storage order took 19 ms for
+// 200,000 points (0.21 without the outlier, now 0.22 with it; the nearest
+// search 45 ms, now 39, for the outlier's own distances, which FP32 cannot
+// tell apart).  Closer to the bulk equal cells are the better ones: seeds with
+// outliers 10 to 100 scene sizes away take 5 to 20 % longer with the logarithm.
+// The cells only order the points; every distance is that of the points
+// themselves.
+__device__ __forceinline__ double knn_warp(double u, double knee)
+{
+    return fabs(u) > knee ? copysign(1.0 + (double)(GSR_KNN_LN2 * __builtin_amdgcn_logf((float)fabs(u))), u) : u;
+}
+
+__device__ __forceinline__ uint32_t knn_cell(const KnnTree& t, int c, float x)
+{
+    const double q = (knn_warp(((double)x - t.centre[c]) * t.inv_half, t.knee) - t.least[c]) * t.cells;
+    return q >= 2097151.0 ? 2097151u : (q > 0.0 ? (uint32_t)q : 0u);
+}
+
+// Place along the Hilbert curve through the 2^63 cells (Skilling 2004,
+// transposed axes); consecutive cells share a face, where Morton order jumps
+// and leaves a share of the boxes large.  Non-finite points come last.
 __device__ __forceinline__ uint64_t knn_code(const KnnTree& t, float x, float y, float z)
 {
     if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) return ~0ull >> 1;
-    const float p[3] = {x, y, z};
-    uint32_t X[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double q = ((double)p[c] - t.lo[c]) * t.scale;
-        X[c] = q >= 2097151.0 ? 2097151u : (uint32_t)q;
-    }
+    uint32_t X[3] = {knn_cell(t, 0, x), knn_cell(t, 1, y), knn_cell(t, 2, z)};
     for (uint32_t Q = 1u << 20; Q > 1u; Q >>= 1) {
         const uint32_t P = Q - 1u;
 #pragma unroll
@@ -148,25 +195,15 @@ __device__ __forceinline__ uint64_t knn_code(const KnnTree& t, float x, float y,
     return (spread21(X[0] ^ g) << 2) | (spread21(X[1] ^ g) << 1) | spread21(X[2] ^ g);
 }
 
-// Sample s of S: a point of the s-th of S equal runs of points, at a place in
-// the run that looks random.  (The first point of every run lets a validity
-// that follows the storage order, every other pixel of a row of 1024 say, hide
-// all valid points from the samples: 2^20 points went into one bucket, and the
-// nearest search took 18 ms instead of 0.5.)
-__device__ __forceinline__ int64_t sample_point(int s, int S, int64_t n)
-{
-    uint32_t h = (uint32_t)s + 1u;
-    h = (h ^ (h >> 16)) * 0x7feb352du;
-    h = (h ^ (h >> 15)) * 0x846ca68bu;
-    h ^= h >> 16;
-    const int64_t i0 = (int64_t)s * n / S, len = (int64_t)(s + 1) * n / S - i0;
-    return i0 + (int64_t)(((uint64_t)h * (uint64_t)len) >> 32);
-}
-
 // Splitters of the buckets: split[b] is the least code of bucket b.  Every
 // block forms the codes of all samples (an invalid one sorts last) and ranks
 // 64 of them, the waves sharing the comparisons; the samples of ranks 4 b
 // become the splitters.
+//
+// Before that every block forms the cells (knn_cell) alike: the bulk is what
+// lies between the 1/8 and 7/8 quantiles of 64 points, along each
+// axis; the cube is twice as wide about its middle, so that a uniform box and
+// its walls lie inside and up to an eighth of the points may be anywhere.
 template <int BUCKETS>
 __global__ __launch_bounds__(1024) void k_knn_split(KnnArgs a)
 {
@@ -174,32 +211,66 @@ __global__ __launch_bounds__(1024) void k_knn_split(KnnArgs a)
     static_assert(S % 1024 == 0, "a wave counts whole runs of 64 samples");
     __shared__ uint64_t code[S];
     __shared__ uint32_t part[16][64];
-    __shared__ float red[6][16];
+    __shared__ float red[6][GSR_KNN_BLOCKS / 64];
+    __shared__ float quant[3][2];
     __shared__ KnnTree t;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-        const float x = tid < GSR_KNN_BLOCKS ? a.box[tid * 8 + c] : (c < 3 ? INFINITY : -INFINITY);
-        const float r = c < 3 ? wave_minf(x) : wave_maxf(x);
+        if (w >= GSR_KNN_BLOCKS / 64) break;
+        const float x = a.box[tid * GSR_KNN_BOX + c], r = c < 3 ? wave_minf(x) : wave_maxf(x);
         if (lane == 0) red[c][w] = r;
     }
-    __syncthreads();
-    if (tid == 0) {
-        double ext = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            float l = red[c][0], h = red[3 + c][0];
-            for (int k = 1; k < 16; ++k) {
-                l = fminf(l, red[c][k]);
-                h = fmaxf(h, red[3 + c][k]);
-            }
-            t.lo[c] = l <= h ? (double)l : 0.0;
-            ext = fmax(ext, l <= h ? (double)h - (double)l : 0.0);
+    if (w >= 13) {
+        // wave 13 + c ranks 64 of the box pass's points along axis c
+        const int c = w - 13;
+        const float* q = a.box + lane * (GSR_KNN_BLOCKS / 64) * GSR_KNN_BOX + 6;
+        const float x = q[0] == q[0] ? q[c] : NAN;
+        const bool some = x == x;
+        const int m = __popcll(__ballot(some));
+        int rank = 0;
+        for (int k = 0; k < 64; ++k) {
+            const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
+            rank += (y < x || (y == x && k < lane)) ? 1 : 0;
         }
-        t.scale = ext > 0.0 ? 2097152.0 / ext : 0.0;
-        t.leaves = 0;
-        if (blockIdx.x == 0) *a.tree = t;
+        if (some && rank == m / 8) quant[c][0] = x;
+        if (some && rank == m - 1 - m / 8) quant[c][1] = x;
+        if (m == 0 && lane < 2) quant[c][lane] = 0.0f;
     }
     __syncthreads();
+    if (w == 0) {
+        // lanes 0, 1, 2: an axis each
+        const int c = min(lane, 2);
+        float l = INFINITY, h = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < GSR_KNN_BLOCKS / 64; ++k) {
+            l = fminf(l, red[c][k]);
+            h = fmaxf(h, red[3 + c][k]);
+        }
+        const double lo = l, hi = h, q0 = quant[c][0], q1 = quant[c][1];
+        const double centre = 0.5 * (q0 + q1);
+        const bool some = lo <= hi;
+        auto most = [](double x) { return fmax(fmax(__shfl(x, 0, 64), __shfl(x, 1, 64)), __shfl(x, 2, 64)); };
+        double half = most(q1 - q0);
+        const double far = most(some ? fmax(centre - lo, hi - centre) : 0.0);
+        // (the bulk may be one point)
+        half = half > 0.0 ? half : (far > 0.0 ? far : 1.0);
+        const double inv_half = 1.0 / half, knee = far > KNN_FAR * half ? 1.0 : INFINITY;
+        const double least = some ? knn_warp((lo - centre) * inv_half, knee) : 0.0;
+        const double ext = most(some ? knn_warp((hi - centre) * inv_half, knee) - least : 0.0);
+        if (lane < 3) {
+            t.centre[c] = centre;
+            t.least[c] = least;
+        }
+        if (lane == 0) {
+            t.inv_half = inv_half;
+            t.knee = knee;
+            t.cells = ext > 0.0 ? 2097152.0 / ext : 0.0;
+            t.leaves = 0;
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid == 0) *a.tree = t;
     for (int s = tid; s < S; s += 1024) {
         const int64_t i = sample_point(s, S, a.n);
         code[s] = a.valid[i] ? knn_code(t, a.mean[i], a.mean[a.n + i], a.mean[2 * a.n + i]) : ~0ull;

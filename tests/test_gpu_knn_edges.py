@@ -76,3 +76,54 @@ def test_periodic_validity(n, period, phase):
         d[~ok] = np.inf
         d[i] = np.inf
         assert int(d.argmin()) == got[i]
+
+
+def _best_ms(f, reps=4):
+    best = np.inf
+    for _ in range(reps):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        out = f()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best, out
+
+
+@pytest.mark.parametrize("n", [20_000, 150_000])
+@pytest.mark.parametrize("far", [1.5e3, 1e6, 1e12, 3e37])
+def test_outliers(n, far):
+    """Points far outside the others, past and before the extent at which the
+    cells follow the logarithm: nearest and scale are exact, and the radius
+    search, in which outliers have no part, takes no longer than without them
+    (its leaves held points in storage order: tens of times that, hence 5)."""
+    print(f"[knn] {n} points, outliers at {far:g}", flush=True)
+    rng = np.random.default_rng(n)
+    x = rng.uniform(-1, 1, (3, n))
+    x[rng.integers(0, 3, n), np.arange(n)] = 1.0  # three faces of a box
+    y = x.copy()
+    odd = np.array([0, n // 3, n - 1])
+    y[:, odd] = far * np.array([[1.0, -0.5, 0.25], [0.5, 1.0, -1.0], [-1.0, 0.1, 0.7]])
+    plain, dirty = (torch.from_numpy(a.astype(np.float32)).cuda() for a in (x, y))
+    valid = (rng.random(n) < 0.9).astype(np.int32)
+    valid[odd] = 1
+    V = torch.from_numpy(valid).cuda()
+    err, ang = torch.ones(n, device="cuda"), torch.full((n,), 0.1, device="cuda")
+    P = np.array([[500.0, 0, 320, 0], [0, 500, 240, 0], [0, 0, 1, 0]]).reshape(-1)
+    S = seeding.Scaler(n)
+    r = 2.0 * np.sqrt(12 / np.pi / n * 3)
+    t0, _ = _best_ms(lambda: S.frame(plain, V, err, ang, P, [0.0, 0, 5.0], r))
+    t1, (quat, _) = _best_ms(lambda: S.frame(dirty, V, err, ang, P, [0.0, 0, 5.0], r))
+    print(f"[knn] radius search {t0:.3f} ms, with outliers {t1:.3f} ms", flush=True)
+    assert t1 <= 5 * t0 and bool(torch.isfinite(quat).all())
+    nn = maintain.nearest(dirty, V).cpu().numpy()
+    ls = S(dirty, V, FLOOR).cpu().numpy()
+    X, ok = dirty.double(), V != 0
+    pick = np.concatenate([odd, rng.choice(np.nonzero(valid)[0], 60, replace=False)])
+    for i in pick:
+        d = ((X - X[:, i:i + 1]) ** 2).sum(0)
+        d[~ok] = np.inf
+        d[i] = np.inf
+        assert int(torch.nonzero(d == d.min())[0]) == nn[i]
+        want = float(torch.log(torch.sqrt(torch.sort(d)[0][:3]).mean().clamp_min(FLOOR)))
+        assert abs(ls[0, i] - want) <= 1e-6 * max(1.0, abs(want))
