@@ -5,6 +5,8 @@ import numpy as np
 import pytest
 import torch
 
+from tests import test_gpu_knn
+
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
@@ -127,3 +129,10 @@ def test_outliers(n, far):
         assert int(torch.nonzero(d == d.min())[0]) == nn[i]
         want = float(torch.log(torch.sqrt(torch.sort(d)[0][:3]).mean().clamp_min(FLOOR)))
         assert abs(ls[0, i] - want) <= 1e-6 * max(1.0, abs(want))
+
+
+@pytest.mark.parametrize("kind,n,share", [(k, n, s) for k, s in (("box", 1.0), ("cluster", 0.95))
+                                          for n in (1_049_599, 1_049_600, 1_200_000)])
+def test_larger_buckets(kind, n, share):
+    """From 1,049,600 points on a bucket is sorted 8192 keys at a time."""
+    test_gpu_knn.test_nearest_and_scale(kind, n, share)
