@@ -53,7 +53,7 @@ struct SegArgs {
     const uint32_t* order;     // tiles by pair count, descending
     unsigned long long* seg;   // [capacity]: emitted keys, sorted in place per tile (scratch)
     unsigned long long* keys;  // [capacity]: sorted (tile << 32 | depth bits)
-    uint32_t* vals;            // [capacity]: sorted slots
+    uint32_t* vals;            // [capacity]: sorted slots (links of waiting lists before)
     int64_t n;
 };
 

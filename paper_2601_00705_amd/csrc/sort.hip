@@ -17,8 +17,8 @@
 // are first spread over runs of whole coarse bins (one pass through memory)
 // and these sorted one after another with the bins already known.  Where
 // depths coincide (a key has more than GSR_SEG_CROWDED bin-mates on average)
-// the keys are sorted by their digits instead, and runs that cannot be cut
-// by depth are merged.
+// the keys are sorted by their digits instead; a long list that crowds one
+// coarse bin is cut again within that bin (sort_segment).
 //
 // The kernel is bound by LDS traffic and, for the long lists, by the passes
 // over memory (20 bytes a key, 24 more for a long list's three reads less
@@ -31,6 +31,11 @@
 // 4096 keys a block, 4 keys a thread (more, smaller runs of the long lists:
 // 4930 us), 2048 coarse bins (2870 us), pairs written from the threads that
 // ranked them instead of in order through LDS (3750 us).
+//
+// Lists that crowd a bin, 64 of 30,000 keys (spread depths 158 us): a wall
+// with one near outlier 219 us, one depth for all 202, two walls and an outlier
+// 336; as sorted chunks merged pairwise they took
+// 517, 628 and 658, and the digit passes 285, 247 and 535.
 #include "kernels.h"
 
 namespace gsr {
@@ -272,11 +277,18 @@ __device__ __forceinline__ uint32_t scan_bins(uint32_t* cnt, int K, SegLds<WAVES
     return q;
 }
 
-// A list's (chunk's) coarse bins, as the fine bins need them.
+// A long list's coarse bins, as the fine bins need them: linear over (key -
+// lo) >> shift, the depth bits where shift is 32 and lo's low word 0.
 struct Coarse {
-    uint32_t lo;              // least depth bits
-    unsigned long long mult;  // coarse_mult of their range
+    unsigned long long lo;
+    int shift;
+    unsigned long long mult;  // coarse_mult of the range
 };
+
+__device__ __forceinline__ uint32_t bin_of(const Coarse& c, unsigned long long k)
+{
+    return (uint32_t)(((unsigned long long)(uint32_t)((k - c.lo) >> c.shift) * c.mult) >> 32);
+}
 
 // Sorts the m <= ITEMS unique keys src[0, m) with the whole block; on return
 // (after a barrier) key[r] of thread (w, lane) holds the key of sorted
@@ -299,7 +311,9 @@ __device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, b
         const int li = w * R * 64 + r * 64 + lane;
         key[r] = li < m ? src[li] : ~0ull;
     }
-    uint32_t bin[MAXR], rank[MAXR];
+    // a key's fine bin (high half) and its place among the bin's arrivals
+    static_assert(SegLds<WAVES>::ITEMS <= 65536, "both fit in half a word");
+    uint32_t slot[MAXR];
     {
 #pragma unroll
         for (int r = 0; r < MAXR; ++r) {
@@ -310,17 +324,23 @@ __device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, b
         // start
         if (known) {
             __syncthreads();
+            auto place = [&](auto&& place_of) {
 #pragma unroll
-            for (int r = 0; r < MAXR; ++r) {
-                if (r >= R) break;
-                const int li = w * R * 64 + r * 64 + lane;
-                if (li < m) {
-                    const unsigned long long p = (unsigned long long)((uint32_t)(key[r] >> 32) - in_list.lo) * in_list.mult;
-                    const uint32_t b = (uint32_t)(p >> 32), s = L.starts[b], e = L.starts[b + 1];
-                    bin[r] = s - done + __umulhi((uint32_t)p, e - s);
-                    rank[r] = atomicAdd(&L.fine[bin[r]], 1u);
+                for (int r = 0; r < MAXR; ++r) {
+                    if (r >= R) break;
+                    const int li = w * R * 64 + r * 64 + lane;
+                    if (li < m) {
+                        const unsigned long long p = (unsigned long long)place_of(key[r]) * in_list.mult;
+                        const uint32_t b = (uint32_t)(p >> 32), s = L.starts[b], e = L.starts[b + 1];
+                        const uint32_t bin = s - done + __umulhi((uint32_t)p, e - s);
+                        slot[r] = bin << 16 | atomicAdd(&L.fine[bin], 1u);
+                    }
                 }
-            }
+            };
+            if (in_list.lo << 32 == 0ull && in_list.shift == 32)
+                place([&](unsigned long long k) { return (uint32_t)(k >> 32) - (uint32_t)(in_list.lo >> 32); });
+            else
+                place([&](unsigned long long k) { return (uint32_t)((k - in_list.lo) >> in_list.shift); });
         } else {
             uint32_t lo = 0xffffffffu, hi = 0u;
 #pragma unroll
@@ -353,8 +373,8 @@ __device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, b
                 if (li < m) {
                     const unsigned long long p = (unsigned long long)((uint32_t)(key[r] >> 32) - lo) * mult;
                     const uint32_t b = (uint32_t)(p >> 32), s = L.coarse[b], e = L.coarse[b + 1];
-                    bin[r] = s + __umulhi((uint32_t)p, e - s);
-                    rank[r] = atomicAdd(&L.fine[bin[r]], 1u);
+                    const uint32_t bin = s + __umulhi((uint32_t)p, e - s);
+                    slot[r] = bin << 16 | atomicAdd(&L.fine[bin], 1u);
                 }
             }
         }
@@ -371,24 +391,24 @@ __device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, b
 #pragma unroll
     for (int r = 0; r < MAXR; ++r) {
         if (r >= R) break;
-        if (w * R * 64 + r * 64 + lane < m) L.sk[L.fine[bin[r]] + rank[r]] = key[r];
+        if (w * R * 64 + r * 64 + lane < m) L.sk[L.fine[slot[r] >> 16] + (slot[r] & 0xffffu)] = key[r];
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < MAXR; ++r) {
         if (r >= R) break;
         if (w * R * 64 + r * 64 + lane < m) {
-            const uint32_t s = L.fine[bin[r]], e = L.fine[bin[r] + 1];
-            rank[r] = s;
+            const uint32_t s = L.fine[slot[r] >> 16], e = L.fine[(slot[r] >> 16) + 1];
+            slot[r] = s;  // from here on its sorted position
             if (e - s > 1u)
-                for (uint32_t j = s; j < e; ++j) rank[r] += L.sk[j] < key[r] ? 1u : 0u;
+                for (uint32_t j = s; j < e; ++j) slot[r] += L.sk[j] < key[r] ? 1u : 0u;
         }
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < MAXR; ++r) {
         if (r >= R) break;
-        if (w * R * 64 + r * 64 + lane < m) L.sk[rank[r]] = key[r];
+        if (w * R * 64 + r * 64 + lane < m) L.sk[slot[r]] = key[r];
     }
     __syncthreads();
 #pragma unroll
@@ -398,32 +418,6 @@ __device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, b
         if (li < m) key[r] = L.sk[li];
     }
     __syncthreads();
-}
-
-// Merges the sorted runs A[0, na) and B[0, nb) (unique keys) with the whole
-// block: thread t produces the outputs [t per, (t + 1) per), per =
-// ceil((na + nb) / THREADS), finding how many of them come from A by a
-// binary search along its first diagonal (merge path), then merging
-// sequentially.  out(d, key) receives output position d.
-template <int THREADS, class Out>
-__device__ __forceinline__ void merge_runs(const unsigned long long* A, int na, const unsigned long long* B, int nb,
-                                           Out&& out)
-{
-    const int n = na + nb;
-    const int per = (n + THREADS - 1) / THREADS;
-    const int d0 = min(n, (int)threadIdx.x * per), d1 = min(n, d0 + per);
-    if (d0 >= d1) return;
-    int lo = max(0, d0 - nb), hi = min(d0, na);
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (A[mid] < B[d0 - 1 - mid]) lo = mid + 1;
-        else hi = mid;
-    }
-    int i = lo, j = d0 - lo;
-    for (int d = d0; d < d1; ++d) {
-        const bool take_a = j >= nb || (i < na && A[i] < B[j]);
-        out(d, take_a ? A[i++] : B[j++]);
-    }
 }
 
 // f(key) for the keys src[0, m), the block's threads taking them in turn; eight
@@ -444,47 +438,120 @@ __device__ __forceinline__ void for_keys(const unsigned long long* src, int m, F
     for (; i < m; i += THREADS) f(src[i]);
 }
 
+// A value that every lane holds alike, in a scalar register.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+
+__device__ __forceinline__ unsigned long long uniform(unsigned long long x)
+{
+    return ((unsigned long long)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
+}
+
+// The bins of a list of len keys by their range as a whole (as many of their
+// leading bits as 32 hold), which cuts a list of one depth by index; leaves
+// their starts in L.starts.
+template <int WAVES>
+__device__ __forceinline__ Coarse key_bins(const unsigned long long* src, int len, SegLds<WAVES>& L)
+{
+    constexpr int THREADS = WAVES * 64, NC = GSR_SEG_COARSE / THREADS;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    unsigned long long lo = ~0ull, hi = 0ull;
+    for_keys<THREADS>(src, len, [&](unsigned long long k) {
+        lo = min(lo, k);
+        hi = max(hi, k);
+    });
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = min(lo, (unsigned long long)__shfl_xor(lo, off, 64));
+        hi = max(hi, (unsigned long long)__shfl_xor(hi, off, 64));
+    }
+    if (lane == 0) {
+        L.red64[0][w] = lo;
+        L.red64[1][w] = hi;
+    }
+#pragma unroll
+    for (int k = 0; k < NC; ++k) L.starts[tid + k * THREADS] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) {
+        lo = min(lo, L.red64[0][k]);
+        hi = max(hi, L.red64[1][k]);
+    }
+    lo = uniform(lo);
+    const unsigned long long range = uniform(hi) - lo;
+    const int shift = max(0, 32 - (int)__clzll((long long)range));
+    const unsigned long long mult = uniform(coarse_mult((uint32_t)(range >> shift)));
+    const Coarse bins{lo, shift, mult};
+    for_keys<THREADS>(src, len, [&](unsigned long long k) { atomicAdd(&L.starts[bin_of(bins, k)], 1u); });
+    __syncthreads();
+    scan_bins<WAVES, NC>(L.starts, NC, L, [](uint32_t) { return 0u; }, true);
+    return bins;
+}
+
+// A list's keys from src to dst, bin by bin (their starts in L.starts).
+template <int WAVES>
+__device__ __forceinline__ void spread_keys(const unsigned long long* src, unsigned long long* dst, int len, const Coarse& bins,
+                                            SegLds<WAVES>& L)
+{
+    constexpr int THREADS = WAVES * 64;
+    static_assert(SegLds<WAVES>::ITEMS >= GSR_SEG_COARSE, "a cursor per bin");
+    for (int b = threadIdx.x; b < GSR_SEG_COARSE; b += THREADS) L.fine[b] = L.starts[b];
+    if (threadIdx.x == 0) L.starts[GSR_SEG_COARSE] = (uint32_t)len;
+    __syncthreads();
+    for_keys<THREADS>(src, len, [&](unsigned long long k) { dst[atomicAdd(&L.fine[bin_of(bins, k)], 1u)] = k; });
+    __syncthreads();  // the block's own writes are visible to it
+}
+
 // Sorts the segment of one tile with the whole block.  A list of up to ITEMS
 // keys is sorted in LDS.  A longer one is first spread over its coarse depth
 // bins (emission buffer to output key array, the order inside a bin being
 // arbitrary); whole bins are then taken together up to ITEMS keys at a time
-// and sorted in LDS, in place.  Where more than ITEMS keys share one coarse
-// bin, chunks of ITEMS keys are sorted as they stand and merged pairwise
-// (merge path) through global memory, ping-ponging between the two buffers;
-// the last merge reads the emission buffer and writes the final pairs.
+// and sorted in LDS, in place.
+//
+// Where more keys than that (less an eighth, so that the bins can be taken
+// together by their start) share one coarse bin, or a bin that is nearly as
+// large leaves too many small chunks, as with surfaces seen head-on and an
+// outlier, or with one depth for all, the list is spread bin by bin instead.
+// A bin of more than ITEMS keys then becomes a list of its own with bins of
+// its own range (key_bins), smaller by their number: seven rounds at most, two
+// in practice.  Such lists wait in a chain: the first entries of a.vals in
+// their places, which nothing else uses until they are sorted, hold the list's
+// length, its buffer and the next list; in both buffers its places are its
+// own, so the keys move back and forth between the two.
 template <int WAVES>
 __device__ __forceinline__ void sort_segment(const SegArgs& a, uint32_t tile, uint2 rg, SegLds<WAVES>& L)
 {
     constexpr int THREADS = WAVES * 64, MAXR = GSR_SEG_PER_THREAD, ITEMS = SegLds<WAVES>::ITEMS;
     constexpr int NC = GSR_SEG_COARSE / THREADS;
-    const int m = (int)(rg.y - rg.x);
+    constexpr uint32_t NONE = 0xffffffffu;
     const int v = view_of_tile(a.views, (int)tile);
     const uint32_t vbase = (uint32_t)((int64_t)v * a.n);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    unsigned long long* const bufA = a.seg + rg.x;
-    unsigned long long* const bufB = a.keys + rg.x;  // output keys double as scratch
-    const unsigned long long* src = bufA;
-    unsigned long long* cur = nullptr;  // where sorted chunks wait for merging
-    Coarse bins{0u, 0ull};
+    uint32_t at = rg.x, head = NONE;     // the list in hand, those that wait
+    int m = (int)(rg.y - rg.x);
+    const unsigned long long* src = a.seg + at;
+    Coarse bins{0ull, 32, 0ull};
     uint32_t per_start = 0u;
-    int passes = 0;
+    bool in_keys = false;
     if (m > ITEMS) {
         uint32_t lo = 0xffffffffu, hi = 0u;
-        for_keys<THREADS>(bufA, m, [&](unsigned long long k) {
+        for_keys<THREADS>(src, m, [&](unsigned long long k) {
             lo = min(lo, (uint32_t)(k >> 32));
             hi = max(hi, (uint32_t)(k >> 32));
         });
 #pragma unroll
         for (int k = 0; k < NC; ++k) L.starts[tid + k * THREADS] = 0u;
         block_min_max<WAVES>(lo, hi, L);
-        const unsigned long long mult = coarse_mult(hi - lo);
-        for_keys<THREADS>(bufA, m, [&](unsigned long long k) {
+        lo = uniform(lo);
+        hi = uniform(hi);
+        const unsigned long long mult = uniform(coarse_mult(hi - lo));
+        for_keys<THREADS>(src, m, [&](unsigned long long k) {
             atomicAdd(&L.starts[((unsigned long long)((uint32_t)(k >> 32) - lo) * mult) >> 32], 1u);
         });
         __syncthreads();
-        const uint32_t most = scan_bins<WAVES, NC>(L.starts, NC, L, [](uint32_t) { return 0u; }, true);
+        const uint32_t most = uniform(scan_bins<WAVES, NC>(L.starts, NC, L, [](uint32_t) { return 0u; }, true));
+        bins = Coarse{(unsigned long long)lo << 32, 32, mult};
         // (the chunks' cursors need a place each, and tiny chunks do not pay)
         if (most <= (uint32_t)(ITEMS - ITEMS / 8) && (uint32_t)m / ((uint32_t)ITEMS - most) < (uint32_t)ITEMS) {
+            unsigned long long* const bufB = a.keys + rg.x;  // output keys double as scratch
             // chunk of a coarse bin, by its start: the starts of one chunk's
             // bins differ by at most ITEMS - most, so it holds at most ITEMS
             per_start = 0xffffffffu / ((uint32_t)ITEMS - most);
@@ -495,67 +562,80 @@ __device__ __forceinline__ void sort_segment(const SegArgs& a, uint32_t tile, ui
                 if (b == 0 || __umulhi(L.starts[b - 1], per_start) != c) L.fine[c] = L.starts[b];
             }
             __syncthreads();
-            for_keys<THREADS>(bufA, m, [&](unsigned long long k) {
+            for_keys<THREADS>(src, m, [&](unsigned long long k) {
                 const uint32_t b = (uint32_t)(((unsigned long long)((uint32_t)(k >> 32) - lo) * mult) >> 32);
                 bufB[atomicAdd(&L.fine[__umulhi(L.starts[b], per_start)], 1u)] = k;
             });
             __syncthreads();  // the block's own writes are visible to it
             src = bufB;
-            bins = Coarse{lo, mult};
         } else {
-            while (((long long)ITEMS << passes) < m) ++passes;
-            // where the last merge will read from bufA
-            cur = (passes & 1) ? bufA : bufB;
+            src = nullptr;
+            if (lo == hi) bins.mult = 0ull;
         }
     }
-    for (int done = 0; done < m;) {
-        int cm = m - done;
-        if (m > ITEMS) {
-            cm = min(cm, ITEMS);
-            if (!cur) {
-                // up to the first bin of a later chunk
-                const uint32_t c = __umulhi((uint32_t)done, per_start);
-                int b0 = 0, b1 = GSR_SEG_COARSE;
-                while (b0 < b1) {
-                    const int mid = (b0 + b1) >> 1;
-                    if (__umulhi(L.starts[mid], per_start) > c) b1 = mid;
-                    else b0 = mid + 1;
+    for (int done = 0;;) {
+        if (done == m) {
+            if (head == NONE) return;
+            __syncthreads();
+            at = head;
+            m = (int)uniform(a.vals[at]);
+            in_keys = uniform(a.vals[at + 1]) != 0u;
+            head = uniform(a.vals[at + 2]);
+            done = 0;
+            bins.mult = 0ull;
+            src = nullptr;
+        }
+        if (!src) {
+            src = (in_keys ? a.keys : a.seg) + at;
+            unsigned long long* const dst = (in_keys ? a.seg : a.keys) + at;
+            if (bins.mult == 0ull) bins = key_bins<WAVES>(src, m, L);
+            spread_keys<WAVES>(src, dst, m, bins, L);
+            src = dst;
+        }
+        int end = m;
+        if (per_start != 0u) {
+            // up to the first bin of a later chunk
+            const uint32_t c = __umulhi((uint32_t)done, per_start);
+            int b0 = 0, b1 = GSR_SEG_COARSE;
+            while (b0 < b1) {
+                const int mid = (b0 + b1) >> 1;
+                if (__umulhi(L.starts[mid], per_start) > c) b1 = mid;
+                else b0 = mid + 1;
+            }
+            end = (int)uniform(L.starts[b0]);
+        } else if (bins.mult != 0ull) {
+            // the last bin that starts within ITEMS keys
+            int b0 = 0, b1 = GSR_SEG_COARSE;
+            while (b0 < b1) {
+                const int mid = (b0 + b1 + 1) >> 1;
+                if (L.starts[mid] <= (uint32_t)(done + ITEMS)) b0 = mid;
+                else b1 = mid - 1;
+            }
+            end = (int)uniform(L.starts[b0]);
+            if (end == done) {  // it holds more
+                end = (int)uniform(L.starts[b0 + 1]);
+                const uint32_t p = at + (uint32_t)done;
+                if (tid == 0) {
+                    a.vals[p] = (uint32_t)(end - done);
+                    a.vals[p + 1] = in_keys ? 0u : 1u;
+                    a.vals[p + 2] = head;
                 }
-                cm = (int)L.starts[b0] - done;
+                head = p;
+                done = end;
+                continue;
             }
         }
+        const int cm = end - done;
         unsigned long long key[MAXR];
-        lds_sort<WAVES>(src + done, cm, src != bufA, bins, (uint32_t)done, key, L);
+        lds_sort<WAVES>(src + done, cm, bins.mult != 0ull, bins, (uint32_t)done, key, L);
         const int R = (cm + THREADS - 1) / THREADS;
 #pragma unroll
         for (int r = 0; r < MAXR; ++r) {
             if (r >= R) break;
             const int li = w * R * 64 + r * 64 + lane;
-            if (li < cm) {
-                if (cur) cur[done + li] = key[r];
-                else write_pair(a, rg.x + (uint32_t)(done + li), key[r], tile, vbase);
-            }
+            if (li < cm) write_pair(a, at + (uint32_t)(done + li), key[r], tile, vbase);
         }
-        done += cm;
-    }
-    if (!cur) return;
-    __syncthreads();
-    long long width = ITEMS;
-    for (int p = 1; p <= passes; ++p, width *= 2) {
-        unsigned long long* nxt = cur == bufA ? bufB : bufA;
-        for (long long a0 = 0; a0 < m; a0 += 2 * width) {
-            const int na = (int)min(width, m - a0);
-            const int nb = (int)max(0ll, min(width, m - a0 - width));
-            if (p == passes)
-                merge_runs<THREADS>(cur + a0, na, cur + a0 + na, nb, [&](int d, unsigned long long k) {
-                    write_pair(a, rg.x + (uint32_t)(a0 + d), k, tile, vbase);
-                });
-            else
-                merge_runs<THREADS>(cur + a0, na, cur + a0 + na, nb,
-                                    [&](int d, unsigned long long k) { nxt[a0 + d] = k; });
-        }
-        __syncthreads();
-        cur = nxt;
+        done = end;
     }
 }
 
