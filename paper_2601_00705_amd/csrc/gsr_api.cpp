@@ -1044,7 +1044,11 @@ extern "C" gsr_status gsr_covis(int64_t pixels, int32_t n_frames, const float* T
 extern "C" size_t gsr_prune_workspace_bytes(int64_t n)
 {
     if (n < 0 || n > (1ll << 31) - 1) return 0;
-    return sizeof(uint32_t) * (size_t)((n + GSR_PRUNE_CHUNK - 1) / GSR_PRUNE_CHUNK + 1);
+    // (as many counts past GSR_PRUNE_SMALL as there are for it, so that the
+    // size grows with n)
+    const int64_t small = std::min<int64_t>(n, GSR_PRUNE_SMALL);
+    const int64_t blocks = std::max((n + prune_chunk(n) - 1) / prune_chunk(n), (small + prune_chunk(small) - 1) / prune_chunk(small));
+    return sizeof(uint32_t) * (size_t)(blocks + 1);
 }
 
 // the pruning scan over a given block-count buffer (the caller's workspace
@@ -1052,12 +1056,12 @@ extern "C" size_t gsr_prune_workspace_bytes(int64_t n)
 // hold n in range
 static gsr_status prune_run(int64_t n, const int32_t* m_obs, const float* v_vis, const float* log_scale,
                             const float* opacity_logit, const gsr_prune_config* cfg, int32_t* keep_index,
-                            int64_t* kept, uint32_t* block_count, int32_t chunk, void* stream, const char* where)
+                            int64_t* kept, uint32_t* block_count, void* stream, const char* where)
 {
     PruneArgs a{};
     a.n = n;
-    a.chunk = chunk;
-    a.blocks = (int32_t)((n + chunk - 1) / chunk);
+    a.chunk = prune_chunk(n);
+    a.blocks = (int32_t)((n + a.chunk - 1) / a.chunk);
     a.m_obs = m_obs;
     a.v_vis = v_vis;
     a.log_scale = log_scale;
@@ -1094,7 +1098,7 @@ extern "C" gsr_status gsr_prune(int64_t n, const int32_t* m_obs, const float* v_
     if (st != GSR_OK) return st;
     if (!workspace) return fail(GSR_EINVAL, "null argument");
     return prune_run(n, m_obs, v_vis, log_scale, opacity_logit, cfg, keep_index, kept, (uint32_t*)workspace,
-                     GSR_PRUNE_CHUNK, stream, "gsr_prune");
+                     stream, "gsr_prune");
 }
 
 // ---- pruning without allocation --------------------------------------------
@@ -1105,10 +1109,9 @@ extern "C" gsr_status gsr_prune(int64_t n, const int32_t* m_obs, const float* v_
 // device is taken once, with that device current, by hipGetSymbolAddress,
 // and used from then on.  Every call on one GPU shares the array: calls that
 // overlap on one GPU (two streams, two threads) race.  The scan writes every
-// count it later reads, so nothing needs clearing between calls.  Its 65,536
-// counts are one per GSR_PRUNE_CHUNK Gaussians up to 2^25 of them, and one per
-// GSR_PRUNE_CHUNK_MOST above.
-static __device__ __align__(256) uint32_t scratch[GSR_PRUNE_NOALLOC_MAX_N / GSR_PRUNE_CHUNK_MOST];
+// count it later reads, so nothing needs clearing between calls.  It holds a
+// count for each chunk of the most Gaussians it takes.
+static __device__ __align__(256) uint32_t scratch[GSR_PRUNE_NOALLOC_MAX_N / 2048];
 static_assert(sizeof(scratch) == 256 * 1024, "the size that gsr.h states");
 
 static std::mutex g_scratch_mu;
@@ -1145,9 +1148,7 @@ extern "C" gsr_status gsr_prune_noalloc(int64_t n, const int32_t* m_obs, const f
     uint32_t* block_count = nullptr;
     st = scratch_address(&block_count);
     if (st != GSR_OK) return st;
-    const int64_t counts = (int64_t)(sizeof(scratch) / sizeof(scratch[0]));
-    const int32_t chunk = n <= counts * GSR_PRUNE_CHUNK ? GSR_PRUNE_CHUNK : GSR_PRUNE_CHUNK_MOST;
-    return prune_run(n, m_obs, v_vis, log_scale, opacity_logit, cfg, keep_index, kept, block_count, chunk, stream,
+    return prune_run(n, m_obs, v_vis, log_scale, opacity_logit, cfg, keep_index, kept, block_count, stream,
                      "gsr_prune_noalloc");
 }
 
@@ -1311,8 +1312,8 @@ extern "C" gsr_status gsr_keep_list(int64_t n, const int32_t* mask, int32_t* kee
     if (n <= 0 || n > (1ll << 31) - 1) return fail(GSR_EINVAL, "n must lie in [1, 2^31)");
     PruneArgs a{};
     a.n = n;
-    a.chunk = GSR_PRUNE_CHUNK;
-    a.blocks = (int32_t)((n + GSR_PRUNE_CHUNK - 1) / GSR_PRUNE_CHUNK);
+    a.chunk = prune_chunk(n);
+    a.blocks = (int32_t)((n + a.chunk - 1) / a.chunk);
     a.mask = mask;
     a.block_count = (uint32_t*)workspace;
     a.keep_index = keep_index;

@@ -144,8 +144,13 @@ struct MapLossArgs {
 };
 
 #define GSR_ADAM_BLOCKS 1024         // blocks of the gradient-norm pass
-#define GSR_PRUNE_CHUNK 512          // Gaussians per block of the pruning scan (2048: 7 us a pass at 30k for 4)
-#define GSR_PRUNE_CHUNK_MOST 2048    // the same where the fixed scratch would not hold the blocks' counts
+
+// Gaussians per block of the pruning scan: 512, or 2048 past 2^20 of them,
+// where the one block that scans the blocks' counts would take longer than the
+// others gain (30k: a pass 7 us with 2048, 4 with 512; 30M: the three 344 and
+// 453).
+#define GSR_PRUNE_SMALL (1 << 20)
+static inline int32_t prune_chunk(int64_t n) { return n <= GSR_PRUNE_SMALL ? 512 : 2048; }
 
 struct AdamArgs {
     float* p[5];               // planes: mean, quat, log_scale, opacity_logit, colour
@@ -174,7 +179,7 @@ struct CovisArgs {
 
 struct PruneArgs {
     int64_t n;
-    int32_t chunk;             // Gaussians per block, a multiple of 256
+    int32_t chunk;             // prune_chunk(n) Gaussians per block, a multiple of 256
     int32_t blocks;            // ceil(n / chunk)
     const int32_t* m_obs;
     const float* v_vis;

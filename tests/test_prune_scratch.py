@@ -1,6 +1,6 @@
 """The fixed device array of gsr_prune_noalloc: its size is what gsr.h states,
-and the lists are those of gsr_prune where its chunks change (2^25 Gaussians)
-and at the largest n it takes."""
+and the lists are those of gsr_prune and of the rule where the chunks change
+(2^20 Gaussians), in large maps and at the largest n it takes."""
 import os
 import subprocess
 
@@ -21,7 +21,7 @@ def test_size_is_the_documented_one():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [(1 << 25) - 1, 1 << 25, (1 << 25) + 1, (1 << 27) - 100, 1 << 27])
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 4000, (1 << 25) - 1, 1 << 25, (1 << 25) + 1, (1 << 27) - 100, 1 << 27])
 def test_large_maps(n):
     from paper_2601_00705_amd import lib, maintain
     print(f"[prune] n={n}", flush=True)
@@ -39,3 +39,11 @@ def test_large_maps(n):
     assert 0 < m < n and int(kept_b) == m
     assert torch.equal(keep[:m], keep_b[:m])
     assert bool((keep[1:m] > keep[:m - 1]).all())
+    # the rule in float64, away from its thresholds
+    tr = torch.exp(2 * ls.double()).sum(0)
+    al = torch.sigmoid(logit.double())
+    want = (m_obs >= 2) & (v_vis >= 0.3) & (tr <= 1.5 ** 2) & (al >= 0.05)
+    sure = ((tr - 1.5 ** 2).abs() > 1e-6) & ((al - 0.05).abs() > 1e-7) & ((v_vis - 0.3).abs() > 1e-7)
+    got = torch.zeros(n, dtype=torch.bool, device="cuda")
+    got[keep[:m].long()] = True
+    assert bool((got == want)[sure].all())
