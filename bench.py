@@ -2,7 +2,7 @@
 """Throughput of the differentiable Gaussian-splatting renderer on one MI355X.
 
 A step is one pass of the whole path over one batch of views: projection,
-binning (pair emission + LDS radix sort + tile ranges), compositing forward,
+binning (pair emission + per-tile LDS sort + tile ranges), compositing forward,
 the L1 photometric gradient seed, compositing backward and projection
 backward (all parameters and the pose twists).  Inputs are synthetic and
 seeded (paper_2601_00705_amd.scenes) and resident in HBM before timing.

@@ -165,7 +165,8 @@ typedef struct {
     size_t total;     /* workspace bytes */
 } gsr_layout;
 
-/* Sizes derived by a plan (host struct). */
+/* Sizes derived by a plan (host struct).  sort_passes: 8-bit digits of a
+ * per-tile key (4 of the depth, those of the Gaussian index). */
 typedef struct {
     int64_t n, slots, capacity, total_pixels;
     int32_t n_views, total_tiles, sort_passes, tile_bits;
@@ -577,9 +578,10 @@ gsr_status gsr_pair_count(gsr_plan *plan, int64_t *required, int32_t *overflow, 
  * on.  Returns GSR_EINVAL for an unknown group. */
 typedef enum {
     GSR_T_PROJECT = 0,  /* gsr_project's kernel */
-    GSR_T_BIN_EMIT,     /* pair counting, offsets and emission */
+    GSR_T_BIN_EMIT,     /* pair counting, tile ranges and emission (up to 4096
+                           tiles: their processing order too) */
     GSR_T_BIN_SORT,     /* ordering of the pairs */
-    GSR_T_BIN_RANGES,   /* tile ranges and the tiles' processing order */
+    GSR_T_BIN_RANGES,   /* the tiles' processing order */
     GSR_T_RASTER_FWD,   /* compositing forward kernel */
     GSR_T_LOSS_L1,      /* gsr_loss_l1's kernel */
     GSR_T_CLEAR_GRAD2D, /* zeroing of the screen-space gradient accumulators */

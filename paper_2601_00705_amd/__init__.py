@@ -1,7 +1,7 @@
 """MI355X-native differentiable 3D Gaussian-splatting rasterizer (gfx950 HIP).
 
 The renderer of RGS-SLAM (arXiv 2601.00705): projection with EWA covariance
-(Eq. proj), tile binning with an LDS radix sort, front-to-back compositing
+(Eq. proj), tile binning with a per-tile LDS sort, front-to-back compositing
 (Eq. alpha) and its backward, including the SE(3) pose tangent (Eqs. muCjac,
 muIjac, sigmaIjac).  Every step runs in the HIP kernels of ``libgsr.so``;
 this package only marshals arguments.  Submodules are imported lazily so

@@ -522,8 +522,8 @@ __global__ __launch_bounds__(256) void k_bin_tiles(BinArgs a)
 }
 
 // The same for at most GSR_ONE_TILES tiles, in one block, which also places
-// them in the processing order: instead of this, k_order_count and
-// k_order_place, each 4 to 5 us of a 242 us step.
+// them in the processing order: one launch for this and k_order_place, each 4
+// to 5 us of a 242 us step.
 __global__ __launch_bounds__(1024) void k_bin_tiles_one(BinArgs a)
 {
     constexpr int PER = GSR_ONE_TILES / 1024, NB = GSR_ONE_TILES / GSR_COL_TILES;

@@ -7,7 +7,8 @@
 // grid.  The points are sorted along a Hilbert curve instead and cut
 // into leaves of 64 consecutive points, one wave's worth, each with its
 // bounding box and those of its 8 groups of 8; the leaves' size follows the
-// local density by itself.  A wave takes one leaf as its 64 queries: their
+// local density by itself, and cells that outliers would make coarse are
+// warped (knn_cell).  A wave takes one leaf as its 64 queries: their
 // own leaf gives each query a first bound, then the leaves whose box lies
 // within some query's bound are scanned from LDS.
 //
@@ -27,12 +28,16 @@
 //
 // The box tests and the candidates' prefilter run in FP32 with margins above
 // their rounding; every decision is taken in double on (distance, index), so
-// the result does not depend on the tree.
+// which points are found does not depend on the tree.  The moments of the
+// radius search are sums in double in the order of the leaves; where a bucket
+// is larger than its LDS the points' order in them is arbitrary, and the last
+// bits may differ from call to call.
 //
 // Measured on MI355X, the whole call: the 3 nearest of 500,000 triangulated
-// seeds 0.51 ms (queries 0.31, build 0.20), against 5.0 ms for hashed grid
-// levels with an exhaustive search for far seeds; the nearest of 1M points on
-// a room's walls 0.38 ms (queries 0.11), against 1.6 ms; 1,000 points 16 us,
+// seeds 0.53 to 0.8 ms over ten inputs (queries 0.35 of 0.55, build 0.20),
+// against 4.9 to 6.3 ms for hashed grid levels with an exhaustive search for
+// far seeds; the nearest of 1M points on a room's walls 0.37 to 0.39 ms
+// (queries 0.11; 0.5 for one input of ten), against 1.8 ms; 1,000 points 16 us,
 // against 0.6 ms over 38 launches.  The queries are bound by VALU issue.
 // Tried: a tree of fan-out 8 walked by every lane for itself, 2.2 ms for the
 // same seeds (a node is a gather of 192 bytes per lane); Morton order, whose

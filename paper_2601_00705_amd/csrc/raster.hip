@@ -630,8 +630,8 @@ __global__ __launch_bounds__(64, 5) void k_raster_fwd(RasterArgs a)
 // two and a half times its issue (the chain of LDS read, alpha, T and the
 // branches): 12 tiles of 716 entries 196 us, 1200 tiles of 162 (up to 332)
 // entries 92 us, 825 of 104 77 us.  In four parts of one pixel a lane, four
-// entries at a time, these take 65, 46 and 31 us; 3225 tiles of 318 entries,
-// in two parts, 197 -> 154 us (in four 182: the parts' record reads fill the
+// entries at a time, these take 67, 46 and 32 us; 3225 tiles of 318 entries,
+// in two parts, 197 -> 155 us (in four 182: the parts' record reads fill the
 // LDS; two entries at a time 162; records read ahead into registers 174).
 template <int PPT, int PARTS, int GSR_BATCH, bool COUNT, bool MIXED>
 __global__ __launch_bounds__(64, PPT / PARTS <= 2 ? 6 : 4) void k_raster_fwd_few(RasterArgs a)
@@ -1055,9 +1055,9 @@ __global__ __launch_bounds__(64, PPT <= 4 ? 5 : 3) void k_raster_bwd(RasterArgs 
 // double-buffered, so a group costs one barrier, and a batch is staged while
 // the one before is replayed.  A lone wave's entry takes 1000 cycles, twice
 // its issue; here a group of 8 takes as long as its replay or its reduction,
-// about 2700.  12 tiles of 716 entries 297 -> 101 us (the same waves doing
+// about 2700.  12 tiles of 716 entries 297 -> 104 us (the same waves doing
 // both in turn 156), 1200 tiles of 162 137 -> 100, 825 of 104 in deterministic
-// mode 150 -> 76, 1200 tiles of 512 pixels 743 -> 550 us; but 2400 tiles of 256
+// mode 150 -> 78, 1200 tiles of 512 pixels 743 -> 550 us; but 2400 tiles of 256
 // pixels 684 -> 796 us: the passes through LDS are issue that a full chip
 // lacks, hence GSR_BWD_FEW_TILES (1.5 tiles to a SIMD).
 template <int PPT>

@@ -34,8 +34,8 @@
 //
 // Lists that crowd a bin, 64 of 30,000 keys (spread depths 158 us): a wall
 // with one near outlier 219 us, one depth for all 202, two walls and an outlier
-// 336; as sorted chunks merged pairwise they took
-// 517, 628 and 658, and the digit passes 285, 247 and 535.
+// 336; as sorted chunks merged pairwise they took 517, 628 and 658, in the
+// digit passes 285, 247 and 535.
 #include "kernels.h"
 
 namespace gsr {
@@ -71,9 +71,7 @@ struct SegLds {
     };
     union {
         uint32_t fine[ITEMS + 1];            // fine counts, then starts
-        struct {
-            uint32_t wcnt[WAVES][256];       // radix sort: per-wave digit counters, then wave offsets
-        };
+        uint32_t wcnt[WAVES][256];           // radix sort: per-wave digit counters, then wave offsets
     };
     uint32_t starts[GSR_SEG_COARSE + 1];     // a long list's coarse bins: counts, then starts
     uint32_t wsum[WAVES], wsum2[WAVES];
@@ -314,78 +312,76 @@ __device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, b
     // a key's fine bin (high half) and its place among the bin's arrivals
     static_assert(SegLds<WAVES>::ITEMS <= 65536, "both fit in half a word");
     uint32_t slot[MAXR];
-    {
 #pragma unroll
-        for (int r = 0; r < MAXR; ++r) {
-            if (r >= R) break;
-            L.fine[tid + r * THREADS] = 0u;
-        }
-        // coarse bin b of c keys is cut into c fine bins, numbered from its
-        // start
-        if (known) {
-            __syncthreads();
-            auto place = [&](auto&& place_of) {
-#pragma unroll
-                for (int r = 0; r < MAXR; ++r) {
-                    if (r >= R) break;
-                    const int li = w * R * 64 + r * 64 + lane;
-                    if (li < m) {
-                        const unsigned long long p = (unsigned long long)place_of(key[r]) * in_list.mult;
-                        const uint32_t b = (uint32_t)(p >> 32), s = L.starts[b], e = L.starts[b + 1];
-                        const uint32_t bin = s - done + __umulhi((uint32_t)p, e - s);
-                        slot[r] = bin << 16 | atomicAdd(&L.fine[bin], 1u);
-                    }
-                }
-            };
-            if (in_list.lo << 32 == 0ull && in_list.shift == 32)
-                place([&](unsigned long long k) { return (uint32_t)(k >> 32) - (uint32_t)(in_list.lo >> 32); });
-            else
-                place([&](unsigned long long k) { return (uint32_t)((k - in_list.lo) >> in_list.shift); });
-        } else {
-            uint32_t lo = 0xffffffffu, hi = 0u;
+    for (int r = 0; r < MAXR; ++r) {
+        if (r >= R) break;
+        L.fine[tid + r * THREADS] = 0u;
+    }
+    // coarse bin b of c keys is cut into c fine bins, numbered from its
+    // start
+    if (known) {
+        __syncthreads();
+        auto place = [&](auto&& place_of) {
 #pragma unroll
             for (int r = 0; r < MAXR; ++r) {
                 if (r >= R) break;
                 const int li = w * R * 64 + r * 64 + lane;
                 if (li < m) {
-                    lo = min(lo, (uint32_t)(key[r] >> 32));
-                    hi = max(hi, (uint32_t)(key[r] >> 32));
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NC; ++k) L.coarse[tid + k * THREADS] = 0u;
-            block_min_max<WAVES>(lo, hi, L);
-            const unsigned long long mult = coarse_mult(hi - lo);
-#pragma unroll
-            for (int r = 0; r < MAXR; ++r) {
-                if (r >= R) break;
-                const int li = w * R * 64 + r * 64 + lane;
-                if (li < m) atomicAdd(&L.coarse[((unsigned long long)((uint32_t)(key[r] >> 32) - lo) * mult) >> 32], 1u);
-            }
-            __syncthreads();
-            scan_bins<WAVES, NC>(L.coarse, NC, L, [](uint32_t) { return 0u; }, true);
-            if (tid == 0) L.coarse[GSR_SEG_COARSE] = (uint32_t)m;
-            __syncthreads();
-#pragma unroll
-            for (int r = 0; r < MAXR; ++r) {
-                if (r >= R) break;
-                const int li = w * R * 64 + r * 64 + lane;
-                if (li < m) {
-                    const unsigned long long p = (unsigned long long)((uint32_t)(key[r] >> 32) - lo) * mult;
-                    const uint32_t b = (uint32_t)(p >> 32), s = L.coarse[b], e = L.coarse[b + 1];
-                    const uint32_t bin = s + __umulhi((uint32_t)p, e - s);
+                    const unsigned long long p = (unsigned long long)place_of(key[r]) * in_list.mult;
+                    const uint32_t b = (uint32_t)(p >> 32), s = L.starts[b], e = L.starts[b + 1];
+                    const uint32_t bin = s - done + __umulhi((uint32_t)p, e - s);
                     slot[r] = bin << 16 | atomicAdd(&L.fine[bin], 1u);
                 }
             }
+        };
+        if (in_list.lo << 32 == 0ull && in_list.shift == 32)
+            place([&](unsigned long long k) { return (uint32_t)(k >> 32) - (uint32_t)(in_list.lo >> 32); });
+        else
+            place([&](unsigned long long k) { return (uint32_t)((k - in_list.lo) >> in_list.shift); });
+    } else {
+        uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+        for (int r = 0; r < MAXR; ++r) {
+            if (r >= R) break;
+            const int li = w * R * 64 + r * 64 + lane;
+            if (li < m) {
+                lo = min(lo, (uint32_t)(key[r] >> 32));
+                hi = max(hi, (uint32_t)(key[r] >> 32));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NC; ++k) L.coarse[tid + k * THREADS] = 0u;
+        block_min_max<WAVES>(lo, hi, L);
+        const unsigned long long mult = coarse_mult(hi - lo);
+#pragma unroll
+        for (int r = 0; r < MAXR; ++r) {
+            if (r >= R) break;
+            const int li = w * R * 64 + r * 64 + lane;
+            if (li < m) atomicAdd(&L.coarse[((unsigned long long)((uint32_t)(key[r] >> 32) - lo) * mult) >> 32], 1u);
         }
         __syncthreads();
-        const uint32_t pairs = scan_bins<WAVES, MAXR>(L.fine, R, L, [](uint32_t c) { return c * c; }, false);
-        if (pairs > GSR_SEG_CROWDED * (uint32_t)m) {
-            // too many keys share (nearly) one depth: compared with each
-            // other they would cost more than the digits do
-            radix_sort<WAVES>(key, m, L);
-            return;
+        scan_bins<WAVES, NC>(L.coarse, NC, L, [](uint32_t) { return 0u; }, true);
+        if (tid == 0) L.coarse[GSR_SEG_COARSE] = (uint32_t)m;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < MAXR; ++r) {
+            if (r >= R) break;
+            const int li = w * R * 64 + r * 64 + lane;
+            if (li < m) {
+                const unsigned long long p = (unsigned long long)((uint32_t)(key[r] >> 32) - lo) * mult;
+                const uint32_t b = (uint32_t)(p >> 32), s = L.coarse[b], e = L.coarse[b + 1];
+                const uint32_t bin = s + __umulhi((uint32_t)p, e - s);
+                slot[r] = bin << 16 | atomicAdd(&L.fine[bin], 1u);
+            }
         }
+    }
+    __syncthreads();
+    const uint32_t pairs = scan_bins<WAVES, MAXR>(L.fine, R, L, [](uint32_t c) { return c * c; }, false);
+    if (pairs > GSR_SEG_CROWDED * (uint32_t)m) {
+        // too many keys share (nearly) one depth: compared with each
+        // other they would cost more than the digits do
+        radix_sort<WAVES>(key, m, L);
+        return;
     }
     if (tid == 0) L.fine[R * THREADS] = (uint32_t)m;
 #pragma unroll
