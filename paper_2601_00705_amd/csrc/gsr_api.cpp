@@ -235,9 +235,11 @@ extern "C" gsr_status gsr_plan_create(int64_t n, int32_t n_views, const gsr_came
     // whose every slot is live, and blocks past a view's live count exit at
     // once
     p->chunk_mult = GSR_BIN_CHUNK_MULT;
-    // (and rows enough for a sparse view's smaller chunks)
+    // (and rows enough for a sparse view's smaller chunks, as far as the count
+    // matrix of a plan of many tiles stays small)
     const int64_t full = (int64_t)GSR_BIN_CHUNK * p->chunk_mult;
-    const int64_t least = std::min<int64_t>((n + GSR_BIN_LEAST - 1) / GSR_BIN_LEAST, GSR_BIN_BLOCKS / n_views);
+    const int64_t least = std::min<int64_t>({(n + GSR_BIN_LEAST - 1) / GSR_BIN_LEAST, GSR_BIN_BLOCKS / n_views,
+                                             std::max<int64_t>((n + 255) / 256, GSR_BIN_MATRIX / (tiles * 4))});
     p->chunks = (int32_t)std::max<int64_t>({1, (n + full - 1) / full, least});
     p->bwd_blocks = (int32_t)((n + 255) / 256);
     if (p->bwd_blocks == 0) p->bwd_blocks = 1;

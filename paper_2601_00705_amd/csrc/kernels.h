@@ -305,6 +305,7 @@ struct FrameArgs {
 #ifndef GSR_BIN_BLOCKS
 #define GSR_BIN_BLOCKS 512          // chunks below which they are made smaller
 #endif
+#define GSR_BIN_MATRIX (64 << 20)   // bytes of the count matrix past which chunks of fewer than 256 add no rows to it
 #ifndef GSR_BIN_CHUNK_MULT
 #define GSR_BIN_CHUNK_MULT 2        // live slots per binning chunk, in units of GSR_BIN_CHUNK
 #endif

@@ -39,3 +39,23 @@ def test_direct_search_needs_no_workspace():
     for n in (1, 1000, 16384):
         assert 0 < raw.gsr_seed_scale_workspace_bytes(n) <= 256
     assert raw.gsr_seed_scale_workspace_bytes(16385) > 256
+
+
+@pytest.mark.parametrize("n", [1, 2_000, 30_000, 120_000, 1_000_000])
+@pytest.mark.parametrize("size", [(64, 48), (1920, 1080), (8192, 6000), (16384, 16384)])
+def test_count_matrix_of_many_tiles(size, n):
+    """A plan's count matrix has a row of one counter per tile for every 256
+    Gaussians at most, or 64 MiB where that is less: few Gaussians in a huge
+    view do not take 512 rows."""
+    from paper_2601_00705_amd.render import Config
+
+    def total(n, w, h):
+        plan = lib.gsr_plan_create(n, [{"width": w, "height": h, "fx": 1.0, "fy": 1.0, "cx": 0.0, "cy": 0.0}], Config(), 1000)
+        try:
+            return lib.gsr_plan_workspace_bytes(plan), lib.gsr_plan_get_info(plan).total_tiles
+        finally:
+            lib.gsr_plan_destroy(plan)
+    have, tiles = total(n, *size)
+    fixed, _ = total(0, *size)  # one row
+    slots = total(n, 16, 16)[0] - total(0, 16, 16)[0]
+    assert have <= fixed + slots + max(4 * tiles * -(-n // 256), 64 << 20) + 4096
