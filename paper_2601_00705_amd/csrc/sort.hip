@@ -32,10 +32,12 @@
 // 4930 us), 2048 coarse bins (2870 us), pairs written from the threads that
 // ranked them instead of in order through LDS (3750 us).
 //
-// Lists that crowd a bin, 64 of 30,000 keys (spread depths 158 us): a wall
-// with one near outlier 219 us, one depth for all 202, two walls and an outlier
-// 336; as sorted chunks merged pairwise they took 517, 628 and 658, in the
-// digit passes 285, 247 and 535.
+// Lists that crowd a bin, 64 of 30,000 keys (spread depths 159 us): a wall
+// with one near outlier 219 us, one depth for all 203, two walls and an outlier
+// 209; as sorted chunks merged pairwise they took 517, 628 and 658, in the
+// digit passes 285, 247 and 535.  One list of 200,000 keys at 419 depths and an
+// outlier: 1.40 ms (spread 1.05); cut again by the key's bits instead of depth
+// bits * n + index, which leaves equal depths to the digits, 2.62.
 #include "kernels.h"
 
 namespace gsr {
@@ -275,17 +277,32 @@ __device__ __forceinline__ uint32_t scan_bins(uint32_t* cnt, int K, SegLds<WAVES
     return q;
 }
 
-// A long list's coarse bins, as the fine bins need them: linear over (key -
-// lo) >> shift, the depth bits where shift is 32 and lo's low word 0.
+// A long list's coarse bins, as the fine bins need them: linear over (value -
+// lo) >> shift of the keys' values.  A value is the key itself (gap 0, and
+// shift 32 leaves the depth bits) or, gap being 2^32 - n, depth bits * n +
+// index: as the indices are below n, the order is the same and the indices of
+// one depth fill their range instead of its first part.
 struct Coarse {
     unsigned long long lo;
     int shift;
+    uint32_t gap;
     unsigned long long mult;  // coarse_mult of the range
 };
 
+__device__ __forceinline__ unsigned long long key_value(uint32_t gap, unsigned long long k)
+{
+    return k - (unsigned long long)(uint32_t)(k >> 32) * gap;
+}
+
+// place of a key among the bins: its bin in the high word of place * mult
+__device__ __forceinline__ uint32_t place_in(const Coarse& c, unsigned long long k)
+{
+    return (uint32_t)((key_value(c.gap, k) - c.lo) >> c.shift);
+}
+
 __device__ __forceinline__ uint32_t bin_of(const Coarse& c, unsigned long long k)
 {
-    return (uint32_t)(((unsigned long long)(uint32_t)((k - c.lo) >> c.shift) * c.mult) >> 32);
+    return (uint32_t)(((unsigned long long)place_in(c, k) * c.mult) >> 32);
 }
 
 // Sorts the m <= ITEMS unique keys src[0, m) with the whole block; on return
@@ -334,10 +351,10 @@ __device__ __forceinline__ void lds_sort(const unsigned long long* src, int m, b
                 }
             }
         };
-        if (in_list.lo << 32 == 0ull && in_list.shift == 32)
+        if (in_list.gap == 0u)
             place([&](unsigned long long k) { return (uint32_t)(k >> 32) - (uint32_t)(in_list.lo >> 32); });
         else
-            place([&](unsigned long long k) { return (uint32_t)((k - in_list.lo) >> in_list.shift); });
+            place([&](unsigned long long k) { return place_in(in_list, k); });
     } else {
         uint32_t lo = 0xffffffffu, hi = 0u;
 #pragma unroll
@@ -442,11 +459,11 @@ __device__ __forceinline__ unsigned long long uniform(unsigned long long x)
     return ((unsigned long long)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
 }
 
-// The bins of a list of len keys by their range as a whole (as many of their
-// leading bits as 32 hold), which cuts a list of one depth by index; leaves
-// their starts in L.starts.
+// The bins of a list of len keys by the range of their depth bits * n + index
+// (as many leading bits as 32 hold), which cuts a list of one depth or of few
+// by index; leaves their starts in L.starts.
 template <int WAVES>
-__device__ __forceinline__ Coarse key_bins(const unsigned long long* src, int len, SegLds<WAVES>& L)
+__device__ __forceinline__ Coarse key_bins(const unsigned long long* src, int len, int64_t n, SegLds<WAVES>& L)
 {
     constexpr int THREADS = WAVES * 64, NC = GSR_SEG_COARSE / THREADS;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -471,11 +488,12 @@ __device__ __forceinline__ Coarse key_bins(const unsigned long long* src, int le
         lo = min(lo, L.red64[0][k]);
         hi = max(hi, L.red64[1][k]);
     }
-    lo = uniform(lo);
-    const unsigned long long range = uniform(hi) - lo;
+    const uint32_t gap = 0u - (uint32_t)n;
+    lo = uniform(key_value(gap, lo));
+    const unsigned long long range = uniform(key_value(gap, hi)) - lo;
     const int shift = max(0, 32 - (int)__clzll((long long)range));
     const unsigned long long mult = uniform(coarse_mult((uint32_t)(range >> shift)));
-    const Coarse bins{lo, shift, mult};
+    const Coarse bins{lo, shift, gap, mult};
     for_keys<THREADS>(src, len, [&](unsigned long long k) { atomicAdd(&L.starts[bin_of(bins, k)], 1u); });
     __syncthreads();
     scan_bins<WAVES, NC>(L.starts, NC, L, [](uint32_t) { return 0u; }, true);
@@ -524,7 +542,7 @@ __device__ __forceinline__ void sort_segment(const SegArgs& a, uint32_t tile, ui
     uint32_t at = rg.x, head = NONE;     // the list in hand, those that wait
     int m = (int)(rg.y - rg.x);
     const unsigned long long* src = a.seg + at;
-    Coarse bins{0ull, 32, 0ull};
+    Coarse bins{0ull, 32, 0u, 0ull};
     uint32_t per_start = 0u;
     bool in_keys = false;
     if (m > ITEMS) {
@@ -544,7 +562,7 @@ __device__ __forceinline__ void sort_segment(const SegArgs& a, uint32_t tile, ui
         });
         __syncthreads();
         const uint32_t most = uniform(scan_bins<WAVES, NC>(L.starts, NC, L, [](uint32_t) { return 0u; }, true));
-        bins = Coarse{(unsigned long long)lo << 32, 32, mult};
+        bins = Coarse{(unsigned long long)lo << 32, 32, 0u, mult};
         // (the chunks' cursors need a place each, and tiny chunks do not pay)
         if (most <= (uint32_t)(ITEMS - ITEMS / 8) && (uint32_t)m / ((uint32_t)ITEMS - most) < (uint32_t)ITEMS) {
             unsigned long long* const bufB = a.keys + rg.x;  // output keys double as scratch
@@ -584,7 +602,7 @@ __device__ __forceinline__ void sort_segment(const SegArgs& a, uint32_t tile, ui
         if (!src) {
             src = (in_keys ? a.keys : a.seg) + at;
             unsigned long long* const dst = (in_keys ? a.seg : a.keys) + at;
-            if (bins.mult == 0ull) bins = key_bins<WAVES>(src, m, L);
+            if (bins.mult == 0ull) bins = key_bins<WAVES>(src, m, a.n, L);
             spread_keys<WAVES>(src, dst, m, bins, L);
             src = dst;
         }
